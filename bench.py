@@ -116,7 +116,8 @@ def attention_flops(w, group_idx: np.ndarray) -> float:
     return 4.0 * d * pairs
 
 
-ATTEND_SOURCES = ("attend_mfma.hip", "attend_common.hpp", "hga_device.hpp", "hga_internal.hpp")
+ATTEND_SOURCES = ("attend_mfma.hip", "attend_common.hpp", "lds_copy.hpp",
+                  "hga_device.hpp", "hga_internal.hpp")
 
 
 def traffic_file(kernel: str, workload_key: str) -> str:

@@ -44,6 +44,7 @@
 
 #include "attend_common.hpp"
 #include "hga_internal.hpp"
+#include "lds_copy.hpp"
 
 namespace hga {
 namespace {
@@ -52,40 +53,10 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;  // keys per LDS tile (= chunk)
 constexpr int kXcds = 8;
-constexpr uint32_t kAbsent = 0xffff0000u;  // an offset past every buffer: reads zeros
 constexpr int kMaxGroupSlots = 512;
-
-// Descriptor words of a raw buffer [base, base + bytes) for the copies below
-// (base address, no stride, num_records = bytes); the operands are uniform.
-__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(base);
-    u32x4 r;
-    r.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
-    r.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32) & 0xffffu);
-    r.z = __builtin_amdgcn_readfirstlane(bytes);
-    r.w = 0x00020000u;
-    return r;
-}
-
-// Copy 16 bytes per lane from buffer offset voff to LDS byte lds + 16*lane.
-__device__ __forceinline__ void copy16_to_lds(const u32x4& rs, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 :
-                 : "v"(voff), "s"(rs), "s"(lds)
-                 : "memory");
-}
-
-// Copy 4 bytes per lane from buffer offset voff to LDS byte lds + 4*lane.
-__device__ __forceinline__ void copy4_to_lds(const u32x4& rs, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dword %0, %1, 0 offen lds"
-                 :
-                 : "v"(voff), "s"(rs), "s"(lds)
-                 : "memory");
-}
 
 // Wait until at most N vector-memory loads of this wavefront are in flight.
 template <int N>
@@ -1007,7 +978,7 @@ hipError_t launch_split_any(const hga_plan& plan, const void* q_rot, int q_chunk
 
 }  // namespace
 
-hipError_t launch_attend_valu(const hga_plan& plan, const void* q_rot, int q_chunk0,
+hipError_t launch_attend_f32(const hga_plan& plan, const void* q_rot, int q_chunk0,
                               int n_q_chunks, const void* k_res, const void* v_res,
                               int64_t res_tokens, const int32_t* res_slot, const void* k_routed,
                               const void* v_routed, const int32_t* group_idx, void* out,
@@ -1086,7 +1057,7 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                                   v_src, src_tokens, k_routed, v_routed, stream);
             if (e != hipSuccess) return e;
         }
-        return launch_attend_valu(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+        return launch_attend_f32(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,
                                   nullptr, stream, k_src, v_src, src_tokens);
     }
@@ -1108,7 +1079,7 @@ hipError_t launch_attend(const hga_plan& plan, const void* q_rot, int q_chunk0, 
                          const int32_t* group_idx, void* out, float* lse, hipEvent_t ev_start,
                          hipEvent_t ev_stop, hipStream_t stream) {
     if (plan.p.dtype == HGA_F32)
-        return launch_attend_valu(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+        return launch_attend_f32(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   res_slot, k_routed, v_routed, group_idx, out, lse, ev_start,
                                   ev_stop, stream);
     // the routed buffers are only read on this path
@@ -1132,7 +1103,7 @@ hipError_t launch_gather_attend(const hga_plan& plan, const void* q_rot, int q_c
                                                   v_res, res_tokens, k_routed, v_routed, stream);
             if (e != hipSuccess) return e;
         }
-        return launch_attend_valu(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+        return launch_attend_f32(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   nullptr, k_routed, v_routed, group_idx, out, lse, ev_start,
                                   ev_stop, stream, k_res, v_res, res_tokens);
     }
