@@ -10,25 +10,12 @@
 // Routed rows are resident rows (group g, row o -> token g*G + o), so their
 // key/value gradients land on those rows.
 //
-// Two forms.  The fused kernel serves units whose r*64 query rows fit one
-// workgroup (r <= 2 at d = 64, r = 1 at d = 128); larger GQA groups take the
-// split pair further below (dQ query-major, dK and dV key-major).
-//
-// Fused work item: (unit, part): a workgroup of NW wavefronts takes NW query
-// tiles of 32 rows of the unit's r*64 (as the forward packs them).  Per 64-key tile
-// the workgroup stages K and V row-major in LDS; per 32-key sub-tile each
-// wavefront computes, for its own 32 queries,
-//   S^T = K.Q^T and dP^T = V.dO^T   (B operands: the wave's Q, dO rows, read
-//                                    from LDS into registers once),
-//   P^T, dS^T elementwise           (each lane owns one query column),
-//   dQ += dS.K                      (A = the lane's own dS values, in registers),
-// and writes dS^T and P^T to its LDS scratch.  The key gradients of the
-// sub-tile sum over every query of the workgroup, so after one barrier the
-// 2*D/32 blocks (dK or dV, 32 dimensions) are split among the wavefronts:
-// each contracts the scratch of all wavefronts against Q^T / dO^T fragments
-// it gathered into registers once, and adds its blocks into the global fp32
-// dk, dv with hardware atomics (other units share visible chunks and routed
-// groups).  No two wavefronts accumulate into the same LDS words.
+// Three kernels: row statistics (D_i, -lse), the key side (dK, dV) and dQ.
+// The key side has two forms: chunk by chunk over the whole sequence
+// (attend_bwd_keys.hip), or unit by unit (below), where a workgroup takes one
+// key tile of one unit, streams the unit's r*64 query rows past it and adds
+// its gradients with atomics, 64*D*2 of them per tile: cheap when r*64 rows
+// share them, the pace of the whole backward when r is small.
 //
 // A product's contraction index may be permuted as long as both operands use
 // the same permutation: dQ's A operand is the lane's own dS^T column (keys in
@@ -37,6 +24,9 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
+#include "attend_bwd.hpp"
 #include "attend_common.hpp"
 #include "hga_internal.hpp"
 
@@ -48,19 +38,6 @@ typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int KT = 64;    // keys per tile (= chunk)
-constexpr int SCR = 40;   // row stride (bf16) of the 32 x 32 scratch tiles
-
-template <int D, int NW>
-struct BwdLayout {
-    static constexpr int KS = D + 8;        // row stride (bf16) of K, V, Q, dO tiles
-    static constexpr int kK = 0;
-    static constexpr int kV = kK + KT * KS * 2;
-    static constexpr int kQ = kV + KT * KS * 2;                  // NW x (Q, dO) rows
-    static constexpr int kScr = kQ + NW * 2 * 32 * KS * 2;       // NW x 2 buffers x (dS^T, P^T)
-    static constexpr int kTok = kScr + NW * 4 * 32 * SCR * 2;    // 2 x (tile row -> token)
-    static constexpr int kGid = kTok + 2 * KT * 4;
-    static constexpr int kBytes = kGid + kMaxTopK * 4;
-};
 
 __device__ __forceinline__ bf16x8_t frag(const bf16_t* p) {
     return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const vec16*>(p));
@@ -135,276 +112,8 @@ __device__ __forceinline__ int tile_token(int tile, int row, int c, const Visibl
     return g >= 0 && g < lim ? (g << group_shift) + (rr & ((1 << group_shift) - 1)) : -1;
 }
 
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attend_bwd_kernel(
-    const bf16_t* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const bf16_t* __restrict__ k_res,
-    const bf16_t* __restrict__ v_res, int64_t res_tokens, const int32_t* __restrict__ group_idx,
-    const bf16_t* __restrict__ out, const float* __restrict__ lse,
-    const bf16_t* __restrict__ dout, float* __restrict__ dq, float* __restrict__ dk,
-    float* __restrict__ dv, int r, int n_kv, int group_shift, int keep_first, int window,
-    int topk_groups, int wg_per_unit, int n_items) {
-    using Lay = BwdLayout<D, NW>;
-    constexpr int NKS = D / 16;   // 16-wide k-steps over d
-    constexpr int NDT = D / 32;   // 32-wide blocks of d
-    constexpr int VPR = D / 8;    // 16-byte vectors per row
-    constexpr int IPW = 2 * NDT / NW;  // key-gradient blocks per wave
-    static_assert(IPW >= 1 && IPW * NW == 2 * NDT, "blocks must split evenly");
-    extern __shared__ __align__(16) unsigned char smem[];
-    bf16_t* sK = reinterpret_cast<bf16_t*>(smem + Lay::kK);
-    bf16_t* sV = reinterpret_cast<bf16_t*>(smem + Lay::kV);
-    bf16_t* sQall = reinterpret_cast<bf16_t*>(smem + Lay::kQ);
-    bf16_t* scr_all = reinterpret_cast<bf16_t*>(smem + Lay::kScr);
-    int* s_tok_all = reinterpret_cast<int*>(smem + Lay::kTok);
-    int* s_gid = reinterpret_cast<int*>(smem + Lay::kGid);
-
-    const int item = blockIdx.x;
-    if (item >= n_items) return;
-    const int unit = item / wg_per_unit, part = item % wg_per_unit;
-    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
-    const int b = bh / n_kv, j = bh % n_kv;
-    const int c = q_chunk0 + i;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, col = lane & 31;
-    const int group = 1 << group_shift, gpc = KT >> group_shift;
-    const int nqt = 2 * r;
-    const int qtile = part * NW + wave;
-    const bool qactive = qtile < nqt;
-    // query tiles of this workgroup that hold queries (a prefix of its waves)
-    const int nqa = min(NW, nqt - part * NW);
-    const int routed_rows = topk_groups * group;
-    const int64_t qtok = static_cast<int64_t>(n_q_chunks) * KT;
-    const int n_q_heads = r * n_kv;
-    // global row of the wave's local query m (0 .. 31)
-    auto qrow_of = [&](int m) {
-        const int row = (qactive ? qtile : 0) * 32 + m;
-        return (static_cast<int64_t>(b) * n_q_heads + j * r + row / KT) * qtok +
-               static_cast<int64_t>(i) * KT + row % KT;
-    };
-    const int t = (qtile * 32 + col) % KT;  // this lane's query token in the chunk
-    const int64_t my_row = qrow_of(col);
-    const float scale2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    const float inv_sqrt_d = 1.0f / sqrtf(static_cast<float>(D));
-
-    for (int s = tid; s < topk_groups; s += NW * 64)
-        s_gid[s] = group_idx[static_cast<int64_t>(unit) * topk_groups + s];
-
-    // The wave's 32 rows of Q and dO stay in LDS, row-major: the B fragments
-    // of S^T = K.Q^T and dP^T = V.dO^T are 16-byte row reads.
-    bf16_t* sQ = sQall + wave * 2 * 32 * Lay::KS;
-    bf16_t* sG = sQ + 32 * Lay::KS;
-    float dsum = 0.f, lse2 = 0.f;
-    if (qactive) {
-        const bf16_t* qp = q_rot + my_row * D;
-        const bf16_t* gp = dout + my_row * D;
-        const bf16_t* op = out + my_row * D;
-        float acc = 0.f;  // D_i = dout_i . out_i over this lane's half of d
-#pragma unroll
-        for (int kk = 0; kk < NKS; ++kk) {
-            const bf16x8_t q8 = frag(qp + kk * 16 + half * 8);
-            const bf16x8_t g8 = frag(gp + kk * 16 + half * 8);
-            const bf16x8_t o8 = frag(op + kk * 16 + half * 8);
-            *reinterpret_cast<bf16x8_t*>(sQ + col * Lay::KS + kk * 16 + half * 8) = q8;
-            *reinterpret_cast<bf16x8_t*>(sG + col * Lay::KS + kk * 16 + half * 8) = g8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                acc = fmaf(static_cast<float>(g8[e]), static_cast<float>(o8[e]), acc);
-        }
-        dsum = add_halves(acc);
-        lse2 = lse[my_row] * 1.4426950408889634f;
-    }
-    lds_barrier();
-
-    // Key-gradient block u of this wave: kind (0: dK from dS^T and Q, 1: dV
-    // from P^T and dO) and 32-dimension block nb.  With NW even the kind is
-    // the wave's parity.  xt[u][q][ks]: B fragment of X^T over query tile q
-    // (the workgroup's q-th), k-step ks: lane holds X[ks*16 + half*8 + e][nb*32 + col].
-    const int kind = wave & 1;
-    bf16x8_t xt[IPW][NW][2];
-#pragma unroll
-    for (int u = 0; u < IPW; ++u) {
-        const int nb = (wave + NW * u) >> 1;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-            const bf16_t* src = sQall + (q * 2 + kind) * 32 * Lay::KS + nb * 32 + col;
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    xt[u][q][ks][e] = q < nqa ? __builtin_bit_cast(
-                                                    __bf16, src[(ks * 16 + half * 8 + e) * Lay::KS])
-                                              : static_cast<__bf16>(0.f);
-        }
-    }
-
-    // B fragments of S^T = K.Q^T and dP^T = V.dO^T (the lane's query row,
-    // dimensions kk*16 + half*8 .. +7), the same for every key tile: read
-    // from LDS once
-    bf16x8_t qf[NKS], gf[NKS];
-#pragma unroll
-    for (int kk = 0; kk < NKS; ++kk) {
-        qf[kk] = frag(sQ + col * Lay::KS + kk * 16 + half * 8);
-        gf[kk] = frag(sG + col * Lay::KS + kk * 16 + half * 8);
-    }
-
-    f32x16_t dqacc[NDT];
-#pragma unroll
-    for (int nb = 0; nb < NDT; ++nb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) dqacc[nb][e] = 0.f;
-
-    const VisibleChunks vis(c, keep_first, window);
-    const int n_vis = vis.count;
-    const int n_rt = (routed_rows + KT - 1) / KT;
-    const int n_tiles = 1 + n_vis + n_rt;
-    const bf16_t* kbase = k_res + static_cast<int64_t>(bh) * res_tokens * D;
-    const bf16_t* vbase = v_res + static_cast<int64_t>(bh) * res_tokens * D;
-    float* gbase = (kind ? dv : dk) + static_cast<int64_t>(bh) * res_tokens * D;
-    const float gscale = kind ? 1.f : inv_sqrt_d;
-    const int lim = c * gpc;  // routed groups must lie in the causal past
-
-    // scratch of wave w, buffer x: dS^T then P^T, each [key][query]
-    auto scratch = [&](int w, int x) { return scr_all + (w * 2 + x) * 2 * 32 * SCR; };
-
-    for (int tile = 0; tile < n_tiles; ++tile) {
-        // Stage K and V row-major (K^T operands are transpose reads of K); the token of each tile row
-        // (-1: a routed row to skip, staged as zeros) goes to the token table
-        // of the tile's parity.  Every wave has passed the previous tile's
-        // last barrier, after which only the token table of that tile's
-        // parity and the scratch are read.  Thread (row, part) issues all its
-        // vectors of the row at once; consecutive threads take consecutive
-        // rows, so the transposed writes are consecutive too.
-        int* s_tok = s_tok_all + (tile & 1) * KT;
-        {
-            constexpr int TPR = NW * 64 / KT;  // threads per row
-            constexpr int VPT = VPR / TPR;     // vectors per thread
-            const int row = tid % KT, pv = tid / KT;
-            const int tok = tile_token(tile, row, c, vis, s_gid, routed_rows, group_shift, lim);
-            if (pv == 0) s_tok[row] = tok;
-            vec16 kx[VPT], vx[VPT];
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) {
-                const int cv = pv * VPT + u;
-                kx[u] = vec16{{0u, 0u, 0u, 0u}};
-                vx[u] = kx[u];
-                if (tok >= 0) {
-                    kx[u] = load16(kbase + static_cast<int64_t>(tok) * D + cv * 8);
-                    vx[u] = load16(vbase + static_cast<int64_t>(tok) * D + cv * 8);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) {
-                const int cv = pv * VPT + u;
-                *reinterpret_cast<vec16*>(sK + row * Lay::KS + cv * 8) = kx[u];
-                *reinterpret_cast<vec16*>(sV + row * Lay::KS + cv * 8) = vx[u];
-            }
-        }
-        lds_barrier();
-        const bool current = tile == 0;
-        for (int st = 0; st < 2; ++st) {
-            if (qactive) {
-                // S^T and dP^T of the 32-key sub-tile st
-                f32x16_t sacc, pacc;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    sacc[e] = 0.f;
-                    pacc[e] = 0.f;
-                }
-                const int krow = st * 32 + col;
-#pragma unroll
-                for (int kk = 0; kk < NKS; ++kk) {
-                    const int off = kk * 16 + half * 8;
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(sK + krow * Lay::KS + off),
-                                                                   qf[kk], sacc, 0, 0, 0);
-                    pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(sV + krow * Lay::KS + off),
-                                                                   gf[kk], pacc, 0, 0, 0);
-                }
-                // P^T, dS^T: lane (half, col) holds keys st*32 + kl, kl below;
-                // element e of fragment kap is e' = kap*8 + e of the accumulator
-                bf16_t* s_dst = scratch(wave, st);
-                bf16_t* s_pt = s_dst + 32 * SCR;
-                bf16x8_t dsf[2];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int kl = (e >> 2) * 8 + half * 4 + (e & 3);
-                    const int key = st * 32 + kl;
-                    const bool ok = s_tok[key] >= 0 && (!current || key <= t);
-                    const float p = __builtin_amdgcn_exp2f(ok ? sacc[e] * scale2 - lse2 : -INFINITY);
-                    const float ds = p * (pacc[e] - dsum);
-                    const __bf16 db = static_cast<__bf16>(ds);
-                    dsf[e >> 3][e & 7] = db;
-                    s_dst[kl * SCR + col] = __builtin_bit_cast(bf16_t, db);
-                    s_pt[kl * SCR + col] = __builtin_bit_cast(bf16_t, static_cast<__bf16>(p));
-                }
-                // dQ += dS.K: k-slot half*8 + e of fragment kap is key
-                // st*32 + kap*16 + (e/4)*8 + half*4 + e%4, so the B operand
-                // is two 4-key runs of dimension nb*32 + col, transpose-read
-                // from the row-major K tile.
-#pragma unroll
-                for (int kap = 0; kap < 2; ++kap)
-#pragma unroll
-                    for (int nb = 0; nb < NDT; ++nb) {
-                        const int k0 = st * 32 + kap * 16 + half * 4;
-                        const bf16x4_t lo = k_tr4(sK, Lay::KS, k0, nb * 32);
-                        const bf16x4_t hi = k_tr4(sK, Lay::KS, k0 + 8, nb * 32);
-                        const bf16x8_t bf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                        dqacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[kap], bf, dqacc[nb], 0, 0, 0);
-                    }
-            }
-            lds_barrier();  // every wave's dS^T, P^T of sub-tile st are in LDS
-            // This wave's key-gradient blocks over the workgroup's queries:
-            // A = dS^T or P^T [key][query] of query tile q, B = xt.
-#pragma unroll
-            for (int u = 0; u < IPW; ++u) {
-                const int nb = (wave + NW * u) >> 1;
-                f32x16_t acc;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-                for (int q = 0; q < NW; ++q) {
-                    if (q < nqa) {
-                        const bf16_t* a = scratch(q, st) + kind * 32 * SCR + col * SCR + half * 8;
-#pragma unroll
-                        for (int ks = 0; ks < 2; ++ks)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a + ks * 16), xt[u][q][ks],
-                                                                          acc, 0, 0, 0);
-                    }
-                }
-                // acc[e]: key st*32 + (e/4)*8 + half*4 + e%4, dimension nb*32 + col
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int tok = s_tok[st * 32 + (e >> 2) * 8 + half * 4 + (e & 3)];
-                    if (tok >= 0)
-                        unsafeAtomicAdd(gbase + static_cast<int64_t>(tok) * D + nb * 32 + col,
-                                        acc[e] * gscale);
-                }
-            }
-        }
-    }
-
-    // dq: C layout [m = query][n = d]: lane column d = nb*32 + col, rows m
-    if (qactive) {
-#pragma unroll
-        for (int nb = 0; nb < NDT; ++nb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int m = (e >> 2) * 8 + half * 4 + (e & 3);
-                dq[qrow_of(m) * D + nb * 32 + col] = dqacc[nb][e] * inv_sqrt_d;
-            }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Split form for units whose query rows span several workgroups (GQA with
-// r = n_q_heads/n_kv_heads > 1): there every workgroup of a unit would add
-// the key gradients of the whole working set, and those fp32 atomics set the
-// pace.  Instead one kernel takes dQ query-major (K/V tiles staged once per
-// eight query tiles) and a second takes dK, dV key-major within the unit:
-// each wavefront keeps 32 keys' K and V fragments and their dK, dV in
-// registers, streams all r*64 query rows of the unit past them, and adds
-// its gradients once.  S and dP are computed by both.
-
-// dQ only: the fused kernel's query side, Q and dO fragments in registers.
+// dQ, query-major: a workgroup stages each key tile of a unit once for up to
+// eight 32-row query tiles, whose Q and dO fragments stay in registers.
 template <int D>
 struct DqLayout {
     static constexpr int KS = D + 8;
@@ -585,12 +294,14 @@ __global__ __launch_bounds__(NW * 64) void attend_bwd_dq_kernel(
     }
 }
 
-// D_i = dout_i . out_i of every query row into dsum (indexed like lse):
-// eight threads per row, each over every eighth 16-byte vector.
+// Row statistics: per 32 query rows (in lse's order), their 32 values of -lse
+// in log2 units, then their 32 of -D_i = -dout_i . out_i.  Eight lanes per
+// row, each over every eighth 16-byte vector.
 template <int D>
-__global__ __launch_bounds__(256) void attend_bwd_dsum_kernel(const bf16_t* __restrict__ out,
+__global__ __launch_bounds__(256) void attend_bwd_stat_kernel(const bf16_t* __restrict__ out,
                                                               const bf16_t* __restrict__ dout,
-                                                              float* __restrict__ dsum, int64_t rows) {
+                                                              const float* __restrict__ lse,
+                                                              float* __restrict__ stat, int64_t rows) {
     constexpr int VPR = D / 8;
     const int64_t row = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) >> 3;
     const int part = threadIdx.x & 7;
@@ -607,7 +318,11 @@ __global__ __launch_bounds__(256) void attend_bwd_dsum_kernel(const bf16_t* __re
     acc += __shfl_xor(acc, 1);
     acc += __shfl_xor(acc, 2);
     acc += __shfl_xor(acc, 4);
-    if (row < rows && part == 0) dsum[row] = acc;
+    if (row < rows && part == 0) {
+        float* at = stat + (row >> 5) * 64 + (row & 31);
+        at[0] = lse[row] * -1.4426950408889634f;
+        at[32] = -acc;
+    }
 }
 
 // dK, dV key-major within a unit.  Work item (unit, tile group): 2*NSUB
@@ -639,7 +354,7 @@ template <int D, int NSUB>
 __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2))) void attend_bwd_kv_kernel(
     const bf16_t* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const bf16_t* __restrict__ k_res,
     const bf16_t* __restrict__ v_res, int64_t res_tokens, const int32_t* __restrict__ group_idx,
-    const float* __restrict__ dsum, const float* __restrict__ lse,
+    const float* __restrict__ stat,
     const bf16_t* __restrict__ dout, float* __restrict__ dk, float* __restrict__ dv, int r, int n_kv,
     int group_shift, int keep_first, int window, int topk_groups, int pairs_per_unit, int n_items) {
     using Lay = KvLayout<D>;
@@ -724,8 +439,8 @@ __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2
             }
         }
         if (sp == 0) {
-            lsex = lse[g];
-            dsx = dsum[g];
+            lsex = stat[(g >> 5) * 64 + (g & 31)];
+            dsx = stat[(g >> 5) * 64 + 32 + (g & 31)];
         }
     };
     auto put = [&](int buf) {
@@ -742,7 +457,7 @@ __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2
             }
         }
         if (sp == 0) {
-            s_stat[sm] = -lsex * 1.4426950408889634f;  // -lse, log2 units
+            s_stat[sm] = lsex;  // -lse, log2 units
             s_stat[32 + sm] = dsx;
         }
     };
@@ -807,7 +522,7 @@ __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2
                     const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
                     for (int x = 0; x < 4; ++x)
-                        af[g4 >> 1][(g4 & 1) * 4 + x] = static_cast<__bf16>(p[x] * (pacc[g4 * 4 + x] - dv4[x]));
+                        af[g4 >> 1][(g4 & 1) * 4 + x] = static_cast<__bf16>(p[x] * (pacc[g4 * 4 + x] + dv4[x]));
                 } else {
 #pragma unroll
                     for (int x = 0; x < 4; ++x) af[g4 >> 1][(g4 & 1) * 4 + x] = static_cast<__bf16>(p[x]);
@@ -853,11 +568,25 @@ __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
+// Whether the key side goes chunk by chunk: always at d64, below eight query
+// heads per KV head at d128, wherever its lists fit.  Whole backward, unit by
+// unit against chunk by chunk (2 x 160 chunks, groups of 16, K_g 12 and 48,
+// us): d64 1 head 653 / 268 and 1540 / 479 (unit by unit: a fused form of it),
+// 4 heads 286 / 231 and 569 / 434, 8 heads 307 / 276 and 597 / 546; d128 2
+// heads 785 / 456 and 1733 / 863, 4 heads 518 / 420 and 1032 / 806, 6 heads
+// 445 / 440 and 892 / 845, 8 heads 517 / 525 and 979 / 1056 (and 32,768
+// tokens, where every unit's rows no longer come from the L2, 3150 / 3500).
+bool by_chunk(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
+    const hga_params& p = plan.p;
+    const int r = p.n_q_heads / p.n_kv_heads;
+    return (p.head_dim == 64 || r < 8) && bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
+}
+
 template <int D, int kNwDq>
-hipError_t launch_bwd_split_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
-                              const void* k_res, const void* v_res, int64_t res_tokens,
-                              const int32_t* group_idx, const void* out, const float* lse,
-                              const void* dout, float* dq, float* dk, float* dv, hipStream_t stream) {
+hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
+                        const void* k_res, const void* v_res, int64_t res_tokens,
+                        const int32_t* group_idx, const void* out, const float* lse,
+                        const void* dout, float* dq, float* dk, float* dv, hipStream_t stream) {
     const hga_params& p = plan.p;
     constexpr int kSub = 2;  // 32-key sub-tiles per key-side workgroup (one tile)
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
@@ -883,22 +612,27 @@ hipError_t launch_bwd_split_t(const hga_plan& plan, const void* q_rot, int q_chu
     const int64_t items_dq = units * wg_per_unit, items_kv = units * pairs;
     if (items_dq > (int64_t(1) << 30) || items_kv > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
     auto grid = [](int64_t n) { return dim3(static_cast<unsigned>((n + kXcds - 1) / kXcds * kXcds)); };
-    // D_i goes to the first rows floats of dq, which the dq kernel (last)
-    // overwrites: no workspace of its own.
+    // The statistics go to the leading floats of dq, which the dq kernel
+    // (last) overwrites: no workspace of its own.
     const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
-    float* dsum = dq;
-    hipLaunchKernelGGL((attend_bwd_dsum_kernel<D>), dim3(static_cast<unsigned>((rows * 8 + 255) / 256)),
+    float* stat = dq;
+    hipLaunchKernelGGL((attend_bwd_stat_kernel<D>), dim3(static_cast<unsigned>((rows * 8 + 255) / 256)),
                        dim3(256), 0, stream, static_cast<const bf16_t*>(out),
-                       static_cast<const bf16_t*>(dout), dsum, rows);
+                       static_cast<const bf16_t*>(dout), lse, stat, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attend_bwd_kv_kernel<D, kSub>), grid(items_kv), dim3(kSub * 128), KvLayout<D>::kBytes, stream,
-                       static_cast<const bf16_t*>(q_rot), q_chunk0, n_q_chunks,
-                       static_cast<const bf16_t*>(k_res), static_cast<const bf16_t*>(v_res), res_tokens,
-                       group_idx, dsum, lse, static_cast<const bf16_t*>(dout),
-                       dk, dv, r, p.n_kv_heads, group_shift, p.keep_first, window, p.topk_groups, pairs,
-                       static_cast<int>(items_kv));
-    e = hipGetLastError();
+    if (by_chunk(plan, q_chunk0, n_q_chunks)) {
+        e = launch_bwd_chunks(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                              group_idx, dout, dq, dk, dv, stream);
+    } else {
+        hipLaunchKernelGGL((attend_bwd_kv_kernel<D, kSub>), grid(items_kv), dim3(kSub * 128),
+                           KvLayout<D>::kBytes, stream, static_cast<const bf16_t*>(q_rot),
+                           q_chunk0, n_q_chunks, static_cast<const bf16_t*>(k_res),
+                           static_cast<const bf16_t*>(v_res), res_tokens, group_idx, stat,
+                           static_cast<const bf16_t*>(dout), dk, dv, r, p.n_kv_heads, group_shift,
+                           p.keep_first, window, p.topk_groups, pairs, static_cast<int>(items_kv));
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attend_bwd_dq_kernel<D, kNwDq>), grid(items_dq), dim3(kNwDq * 64),
                        DqLayout<D>::kBytes, stream, static_cast<const bf16_t*>(q_rot), q_chunk0,
@@ -909,55 +643,12 @@ hipError_t launch_bwd_split_t(const hga_plan& plan, const void* q_rot, int q_chu
     return hipGetLastError();
 }
 
-template <int D, int NW>
-hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
-                        const void* k_res, const void* v_res, int64_t res_tokens,
-                        const int32_t* group_idx, const void* out, const float* lse,
-                        const void* dout, float* dq, float* dk, float* dv, hipStream_t stream) {
-    const hga_params& p = plan.p;
-    constexpr int kLds = BwdLayout<D, NW>::kBytes;
-    static std::atomic<uint64_t> configured{0};  // per instantiation and device
-    const hipError_t ce = once_per_device(configured, plan.device, [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bwd_kernel<D, NW>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    });
-    if (ce != hipSuccess) return ce;
-    const int r = p.n_q_heads / p.n_kv_heads;
-    const int wg_per_unit = (2 * r + NW - 1) / NW;
-    const int64_t items = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * wg_per_unit;
-    if (items > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
-    const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
-    hipLaunchKernelGGL((attend_bwd_kernel<D, NW>), dim3(static_cast<unsigned>(items)),
-                       dim3(NW * 64), kLds, stream, static_cast<const bf16_t*>(q_rot), q_chunk0,
-                       n_q_chunks, static_cast<const bf16_t*>(k_res),
-                       static_cast<const bf16_t*>(v_res), res_tokens, group_idx,
-                       static_cast<const bf16_t*>(out), lse, static_cast<const bf16_t*>(dout), dq,
-                       dk, dv, r, p.n_kv_heads, group_shift, p.keep_first, recent_window(p),
-                       p.topk_groups, wg_per_unit, static_cast<int>(items));
-    return hipGetLastError();
-}
-
-}  // namespace
-
-// One fused kernel when a workgroup holds all of a unit's query tiles (four
-// at d64, two at d128); otherwise the split pair of kernels.
-namespace {
-bool bwd_fused(const hga_params& p) {
-    const int r = p.n_q_heads / p.n_kv_heads;
-    return p.head_dim == 64 ? r <= 2 : r == 1;
-}
 }  // namespace
 
 size_t attend_backward_lds_bytes(const hga_plan& plan) {
-    const hga_params& p = plan.p;
-    const int r = p.n_q_heads / p.n_kv_heads;
-    if (bwd_fused(p)) {
-        if (p.head_dim == 64) return r == 1 ? BwdLayout<64, 2>::kBytes : BwdLayout<64, 4>::kBytes;
-        return BwdLayout<128, 2>::kBytes;
-    }
-    if (p.head_dim == 64)
-        return DqLayout<64>::kBytes > KvLayout<64>::kBytes ? DqLayout<64>::kBytes : KvLayout<64>::kBytes;
-    return DqLayout<128>::kBytes > KvLayout<128>::kBytes ? DqLayout<128>::kBytes : KvLayout<128>::kBytes;
+    const size_t dq = plan.p.head_dim == 64 ? DqLayout<64>::kBytes : DqLayout<128>::kBytes;
+    const size_t kv = plan.p.head_dim == 64 ? KvLayout<64>::kBytes : KvLayout<128>::kBytes;
+    return std::max({dq, kv, bwd_chunks_lds_bytes(plan)});
 }
 
 hipError_t launch_attend_backward(const hga_plan& plan, const void* q_rot, int q_chunk0,
@@ -970,23 +661,16 @@ hipError_t launch_attend_backward(const hga_plan& plan, const void* q_rot, int q
 #define HGA_BWD(DD, NN)                                                                         \
     return launch_bwd_t<DD, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,   \
                                 group_idx, out, lse, dout, dq, dk, dv, stream)
-#define HGA_BWD_SPLIT(DD, NN)                                                                    \
-    return launch_bwd_split_t<DD, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,         \
-                                      res_tokens, group_idx, out, lse, dout, dq, dk, dv, stream)
-    if (!bwd_fused(p)) {
-        // the dq kernel's wavefronts: one per 32-row query tile, up to eight
-        // (the split form starts at r = 3 for d = 64, r = 2 for d = 128)
-        if (p.head_dim == 64) HGA_BWD_SPLIT(64, 8);
-        if (r == 2) HGA_BWD_SPLIT(128, 4);
-        HGA_BWD_SPLIT(128, 8);
-    }
+    // the dq kernel's wavefronts: one per 32-row query tile, up to eight
     if (p.head_dim == 64) {
         if (r == 1) HGA_BWD(64, 2);
-        HGA_BWD(64, 4);
+        if (r == 2) HGA_BWD(64, 4);
+        HGA_BWD(64, 8);
     }
-    HGA_BWD(128, 2);
+    if (r == 1) HGA_BWD(128, 2);
+    if (r == 2) HGA_BWD(128, 4);
+    HGA_BWD(128, 8);
 #undef HGA_BWD
-#undef HGA_BWD_SPLIT
 }
 
 }  // namespace hga

@@ -1,0 +1,519 @@
+// Key gradients of the exact-token attention (Sec. 3.4, Eq. (1)), chunk by
+// chunk: every query unit that attends a key chunk (its own, the recent
+// window's, everybody for a sink, and the units that opened some of its
+// groups) passes by the chunk's keys, whose dK and dV stay in registers and
+// are added to memory once.
+//
+// Unit-major accumulation adds 64 x D x 2 floats with atomics for every
+// (unit, key tile) pair; with one query head per KV head that is one atomic
+// add per 64 products' worth of work, and the L2's atomic rate (about 0.3 T
+// adds/s) sets the pace.  Here the pairs are inverted first:
+//
+//   bwd_index_kernel      one workgroup per (batch, KV head) counts, scans
+//                         and fills, per key chunk, the list of (query unit,
+//                         opened groups) entries, and cuts long lists (sink
+//                         chunks, chunks everybody looks up) into segments.
+//   bwd_chunk_kernel      one workgroup per segment.
+//
+// Both keep their tables in the caller's dq buffer, which the dQ kernel
+// writes afterwards.
+#include <hip/hip_runtime.h>
+#include <math.h>
+
+#include <algorithm>
+
+#include "attend_bwd.hpp"
+#include "attend_common.hpp"
+#include "hga_internal.hpp"
+#include "lds_copy.hpp"
+
+namespace hga {
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef short i16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int KT = 64;    // tokens per chunk
+constexpr int kXcds = 8;
+constexpr int kIndexThreads = 1024;
+
+// A list entry: query unit, its opened groups of the chunk (bit per group),
+// and whether the chunk is the unit's own (causal mask).
+constexpr int kUnitBits = 22, kMaskShift = 22;
+constexpr uint32_t kCausal = 1u << 30;
+static_assert(kBwdIndexChunks <= 1 << kUnitBits, "unit ids");
+// An item: x = chunk | entries << 15 | (part of a cut list) << 30, y = first
+// entry.
+constexpr int kCountShift = 15;
+static_assert(kBwdIndexChunks <= 1 << kCountShift, "chunk ids");
+
+// The tables of one (batch, KV head), `stride` ints apart.
+struct Index {
+    int* base;
+    int stride, cap_items;
+    __device__ int2* items(int bh) const {
+        return reinterpret_cast<int2*>(base + static_cast<int64_t>(bh) * stride);
+    }
+    __device__ uint32_t* entries(int bh) const {
+        return reinterpret_cast<uint32_t*>(items(bh) + cap_items);
+    }
+};
+
+// Calls f(chunk, entry) for every entry of the (batch, KV head), the work
+// spread over the workgroup: slot 0 of unit i is its own chunk, then its
+// visible chunks, then its routed groups, where a run of ascending groups of
+// one chunk makes one entry (any other order, and repeated ids, make several).
+template <typename F>
+__device__ __forceinline__ void each_entry(const int32_t* __restrict__ gid, int nq, int q_chunk0,
+                                           int keep_first, int window, int topk, int gpc_shift,
+                                           FastDiv per, F f) {
+    const int fixed = per.d - topk;
+    const int gpc = 1 << gpc_shift;
+    for (uint32_t idx = threadIdx.x; idx < nq * per.d; idx += kIndexThreads) {
+        const int i = per.div(idx), k = idx - i * per.d;
+        const int c = q_chunk0 + i;
+        const uint32_t all = ((1u << gpc) - 1) << kMaskShift;
+        if (k == 0) {
+            f(c, static_cast<uint32_t>(i) | all | kCausal);
+        } else if (k < fixed) {
+            const VisibleChunks vis(c, keep_first, window);
+            if (k - 1 < vis.count) f(vis.chunk(k - 1), static_cast<uint32_t>(i) | all);
+        } else {
+            const int32_t* g = gid + static_cast<int64_t>(i) * topk;
+            const int s = k - fixed;
+            const int lim = c << gpc_shift;
+            auto valid = [&](int x) { return x >= 0 && x < lim; };
+            const int g0 = g[s];
+            if (!valid(g0)) continue;
+            const int chunk = g0 >> gpc_shift;
+            const int before = s > 0 ? g[s - 1] : -1;
+            if (valid(before) && (before >> gpc_shift) == chunk && before < g0) continue;
+            uint32_t mask = 1u << (g0 & (gpc - 1));
+            for (int last = g0, t = s + 1; t < topk; ++t) {
+                const int gt = g[t];
+                if (!valid(gt) || (gt >> gpc_shift) != chunk || gt <= last) break;
+                mask |= 1u << (gt & (gpc - 1));
+                last = gt;
+            }
+            f(chunk, static_cast<uint32_t>(i) | mask << kMaskShift);
+        }
+    }
+}
+
+// Bound by its two passes over the ids and the LDS counters: a few
+// microseconds beside the kernels it feeds.
+__global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
+    const int32_t* __restrict__ group_idx, int nq, int q_chunk0, int keep_first, int window,
+    int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, Index ix) {
+    extern __shared__ int s_cnt[];  // [n_chunks]
+    __shared__ int s_sum[2][kIndexThreads / 64];
+    const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t* gid = group_idx + static_cast<int64_t>(bh) * nq * topk;
+    for (int x = tid; x < n_chunks; x += kIndexThreads) s_cnt[x] = 0;
+    __syncthreads();
+    each_entry(gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
+               [&](int chunk, uint32_t) { atomicAdd(&s_cnt[chunk], 1); });
+    __syncthreads();
+    // exclusive sums of the entries and of the segments, a run of chunks per thread
+    const int run = (n_chunks + kIndexThreads - 1) / kIndexThreads;
+    const int lo = min(tid * run, n_chunks), hi = min(lo + run, n_chunks);
+    int n_ent = 0, n_seg = 0;
+    for (int x = lo; x < hi; ++x) {
+        n_ent += s_cnt[x];
+        n_seg += (s_cnt[x] + seg - 1) / seg;
+    }
+    int at_ent = wave_incl_scan_add(n_ent), at_seg = wave_incl_scan_add(n_seg);
+    if (lane == 63) {
+        s_sum[0][wave] = at_ent;
+        s_sum[1][wave] = at_seg;
+    }
+    __syncthreads();
+    at_ent -= n_ent;
+    at_seg -= n_seg;
+    for (int w = 0; w < wave; ++w) {
+        at_ent += s_sum[0][w];
+        at_seg += s_sum[1][w];
+    }
+    int2* items = ix.items(bh);
+    for (int x = lo; x < hi; ++x) {
+        const int n = s_cnt[x];
+        s_cnt[x] = at_ent;  // the fill's cursor
+        for (int o = 0; o < n; o += seg)
+            items[at_seg++] = make_int2(x | min(seg, n - o) << kCountShift | (n > seg) << 30,
+                                        at_ent + o);
+        at_ent += n;
+    }
+    // the unused items have no entries
+    if (tid == kIndexThreads - 1) s_sum[0][0] = at_seg;
+    __syncthreads();
+    for (int x = s_sum[0][0] + tid; x < ix.cap_items; x += kIndexThreads) items[x] = make_int2(0, 0);
+    __syncthreads();
+    uint32_t* entries = ix.entries(bh);
+    each_entry(gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
+               [&](int chunk, uint32_t e) { entries[atomicAdd(&s_cnt[chunk], 1)] = e; });
+}
+
+// 16-byte chunk j of staged row r is stored at j ^ swz(r).  The 16-byte
+// fragment reads of 16 consecutive rows then fall in distinct banks, and so
+// do the transpose reads, whose 32 bytes per row come from rows 0..7 or from
+// rows 0..3 and 8..11 of a 16-row block in one cycle.
+template <int D>
+__device__ __forceinline__ int swz(int r) {
+    if constexpr (D == 64)  // two rows span the banks: r >> 1 counts
+        return (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) | ((r >> 3) & 1);
+    else
+        return ((r & 1) << 3) | (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) |
+               ((r >> 3) & 1);
+}
+
+// QR query rows per step, NS steps in the LDS ring.
+template <int D, int QR, int NS>
+struct ChunkLayout {
+    static constexpr int kRow = D * 2;
+    static constexpr int kG = QR * kRow;           // dO rows after the Q rows
+    static constexpr int kStat = 2 * QR * kRow;    // per 32 rows: -lse[32], -D[32]
+    static constexpr int kStage = kStat + QR / 32 * 256;
+    static constexpr int kBytes = NS * kStage;
+};
+
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// One segment: the chunk's 64 keys, 16 to a wavefront (K and V fragments, dK
+// and dV in registers), against the segment's (unit, query head) pairs, 64
+// query rows staged in LDS at a time and shared by the four wavefronts.  Per
+// 32 query rows and wavefront (v_mfma_f32_16x16x32_bf16):
+//   S = Q.K^T, dP = dO.V^T     (A = rows from LDS, B = registers)
+//   P, dS                      (lane = key, registers = queries)
+//   dV += P^T.dO, dK += dS^T.Q (A = the lane's own P, dS; B = transpose reads)
+// The contraction over queries is permuted alike in A and B, so P and dS go
+// from accumulators to operands without leaving the lane.  A wavefront skips
+// the units that opened none of its keys' groups.
+// 16-key wavefronts fit the routed groups exactly (no masked products) and
+// keep the registers low; several workgroups per CU hide each other's
+// barriers and copies.
+//
+// Bound: the query rows' way to the LDS.  With the products left out the
+// kernel takes 400 of its 530-580 us on 8 x 12 heads x 12,288 tokens (3.1 GB
+// staged, 61% from the L2; 0.6 GB of dK and dV read and written), matrix
+// cores 20% busy, VALU 24%, LDS 25%.  Tried at that size: a three-step ring
+// (three workgroups per CU instead of four) 640 us, 32-row steps with three
+// or four in the ring 640-650, 32 keys x 32 rows per wavefront (half the LDS
+// reads, both blocks always computed) 700.  At d128 a 64-row step leaves room
+// for two workgroups per CU and 32 rows for three: 2640 against 2363 us on 32/4
+// heads x 32,768 tokens.
+template <int D, int QR, int NS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+void bwd_chunk_kernel(
+    const bf16_t* __restrict__ q_rot, int q_chunk0, int n_q_chunks,
+    const bf16_t* __restrict__ k_res, const bf16_t* __restrict__ v_res, int64_t res_tokens,
+    const float* __restrict__ stat, const bf16_t* __restrict__ dout,
+    float* __restrict__ dk, float* __restrict__ dv, FastDiv r_div,
+    FastDiv kv_div, FastDiv item_div, int group_shift, Index ix, int n_blocks, int by_xcd) {
+    using Lay = ChunkLayout<D, QR, NS>;
+    constexpr int kRow = Lay::kRow;
+    constexpr int NKS = D / 32;            // 32-wide k-steps over d
+    constexpr int NB = D / 16;             // 16-wide blocks of d
+    constexpr int CPR = D / 8;             // 16-byte chunks per row
+    constexpr int RPC = 64 / CPR;          // rows per copy
+    constexpr int CU = QR / RPC / 4;       // copies per wave, for Q (and dO)
+    constexpr int SPU = KT / QR;           // steps per unit and query head
+    static_assert(CU >= 1, "copy split");
+    constexpr int LPS = 2 * CU + 1;        // loads per wave and step
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+
+    int logical = blockIdx.x;
+    if (by_xcd) {  // a (batch, KV head)'s segments on one XCD: its Q and dO stay in that L2
+        const int per_xcd = (n_blocks + kXcds - 1) / kXcds;
+        logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    }
+    if (logical >= n_blocks) return;
+    const int bh = item_div.div(logical);
+    const int it = logical - bh * item_div.d;
+    const int2 item = ix.items(bh)[it];
+    if (item.x == 0) return;
+    const int chunk = item.x & ((1 << kCountShift) - 1);
+    const int r = r_div.d;
+    const int n_ent = (item.x >> kCountShift) & 0x7fff;  // at most 32
+    const int n_steps = n_ent * r * SPU;
+    const bool shared = (item.x >> 30) & 1;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const int b = kv_div.div(bh), j = bh - b * kv_div.d;
+    const int64_t qtok = static_cast<int64_t>(n_q_chunks) * KT;
+    const int64_t head0 = static_cast<int64_t>(b) * (r * kv_div.d) + static_cast<int64_t>(j) * r;
+    const float scale2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
+
+    // the segment's entries, one per lane
+    const uint32_t elist = lane < n_ent ? ix.entries(bh)[item.y + lane] : 0;
+    uint32_t koff[CU];  // source offset of this lane's copies: row * kRow + unswizzled chunk
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+        const int row = (u * 4 + wave) * RPC + lane / CPR;
+        koff[u] = row * kRow + (((lane % CPR) ^ swz<D>(row)) * 16);
+    }
+    auto issue = [&](int s, int stage) {
+        const int x = s / SPU, ent = r_div.div(x), hh = x - ent * r;
+        const uint32_t e = __builtin_amdgcn_readlane(elist, ent);
+        const int64_t row0 = (head0 + hh) * qtok + static_cast<int64_t>(e & ((1u << kUnitBits) - 1)) * KT +
+                             s % SPU * QR;
+        const u32x4 rq = rsrc_words(q_rot + row0 * D, QR * kRow);
+        const u32x4 rg = rsrc_words(dout + row0 * D, QR * kRow);
+        const uint32_t at = lds0 + stage * Lay::kStage;
+#pragma unroll
+        for (int u = 0; u < CU; ++u) copy16_to_lds(rq, koff[u], at + (u * 4 + wave) * 1024);
+#pragma unroll
+        for (int u = 0; u < CU; ++u) copy16_to_lds(rg, koff[u], at + Lay::kG + (u * 4 + wave) * 1024);
+        // 256 bytes per 32 rows; with fewer blocks than wavefronts several
+        // copy the same one, so that all wait for the same count
+        const int blk = wave % (QR / 32);
+        copy4_to_lds(rsrc_words(stat + 2 * row0 + blk * 64, 256), lane * 4, at + Lay::kStat + blk * 256);
+    };
+
+    // B operands: the lane's key row, dimensions ks*32 + g4*8 .. +7
+    const int key = wave * 16 + l16;
+    const int64_t krow = static_cast<int64_t>(bh) * res_tokens + static_cast<int64_t>(chunk) * KT + key;
+    bf16x8_t kf[NKS], vf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        kf[ks] = __builtin_bit_cast(bf16x8_t, load16(k_res + krow * D + ks * 32 + g4 * 8));
+        vf[ks] = __builtin_bit_cast(bf16x8_t, load16(v_res + krow * D + ks * 32 + g4 * 8));
+    }
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < n_steps) issue(s, s);
+
+    f32x4_t ak[NB], av[NB];  // dK, dV: lane = dimension nb*16 + l16, rows = keys g4*4 + x
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) ak[nb][x] = av[nb][x] = 0.f;
+
+    // this wavefront's bits of an entry's mask, and this lane's own
+    const uint32_t lane_bit = 1u << (kMaskShift + (key >> group_shift));
+    const uint32_t wave_bits =
+        (group_shift == 3 ? 3u << (2 * wave) : 1u << ((wave * 16) >> group_shift)) << kMaskShift;
+
+    // LDS offsets of this lane's reads: the swizzle repeats every 16 rows, so
+    // 16-row blocks are immediates
+    int aoff[NKS], toff[NB];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) aoff[ks] = l16 * kRow + (((ks * 4 + g4) ^ swz<D>(l16)) * 16);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int row = g4 * 4 + (l16 >> 2);  // four queries of one dimension per transpose read
+        toff[nb] = row * kRow + (((nb * 2 + ((l16 & 3) >> 1)) ^ swz<D>(row)) * 16) + (l16 & 1) * 8;
+    }
+    const bool split_groups = group_shift == 3;  // a wavefront's keys are two groups
+
+    int stage = 0;
+    for (int s = 0; s < n_steps; ++s) {
+        if (s + NS - 2 < n_steps)  // that many later steps are in flight
+            wait_copies<(NS - 2) * LPS>();
+        else
+            wait_copies<0>();
+        lds_barrier();  // the step's rows are here; everybody has left the stage before
+        if (s + NS - 1 < n_steps) issue(s + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+        const unsigned char* base = smem + stage * Lay::kStage;
+        stage = stage == NS - 1 ? 0 : stage + 1;
+        const uint32_t e = __builtin_amdgcn_readlane(elist, r_div.div(s / SPU));
+        if (!(e & wave_bits)) continue;
+        const unsigned char* sb = base + Lay::kStat + g4 * 16;
+#pragma unroll
+        for (int pair = 0; pair < QR / 32; ++pair) {
+            f32x4_t sa[2], da[2], nl[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int blk = pair * 2 + h;  // 16-row block
+                nl[h] = *reinterpret_cast<const f32x4_t*>(sb + pair * 256 + h * 64);
+                sa[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                da[h] = *reinterpret_cast<const f32x4_t*>(sb + pair * 256 + 128 + h * 64);  // dP - D
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    const unsigned char* rp = base + aoff[ks] + blk * 16 * kRow;
+                    sa[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, load16(rp)), kf[ks], sa[h], 0, 0, 0);
+                    da[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, load16(rp + Lay::kG)), vf[ks], da[h], 0, 0, 0);
+                }
+            }
+            if (split_groups) {
+                const float kbias = e & lane_bit ? 0.f : -INFINITY;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) nl[h][x] += kbias;
+            }
+            if (e & kCausal) {
+                const int t0 = s % SPU * QR + pair * 32 + g4 * 4;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        nl[h][x] = key <= t0 + h * 16 + x ? nl[h][x] : -INFINITY;
+            }
+            // A operands: k-slot g4*8 + h*4 + x is query pair*32 + h*16 + g4*4 + x
+            bf16x8_t pf, df;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(sa[h][x], scale2, nl[h][x]));
+                    pf[h * 4 + x] = static_cast<__bf16>(p);
+                    df[h * 4 + x] = static_cast<__bf16>(p * da[h][x]);
+                }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const unsigned char* tp = base + toff[nb] + pair * 32 * kRow;
+                auto tr = [&](int off) {
+                    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (lds_i16x4_t*)(reinterpret_cast<uintptr_t>(tp + off)));
+                };
+                const bf16x8_t gb = __builtin_bit_cast(
+                    bf16x8_t, __builtin_shufflevector(tr(Lay::kG), tr(Lay::kG + 16 * kRow), 0, 1, 2, 3, 4, 5, 6, 7));
+                const bf16x8_t qb = __builtin_bit_cast(
+                    bf16x8_t, __builtin_shufflevector(tr(0), tr(16 * kRow), 0, 1, 2, 3, 4, 5, 6, 7));
+                av[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf, gb, av[nb], 0, 0, 0);
+                ak[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df, qb, ak[nb], 0, 0, 0);
+            }
+        }
+    }
+
+    // The chunk's only segment adds in place (nobody else touches its rows in
+    // this launch); the segments of a cut list add atomically.
+    const float ksc = 1.0f / sqrtf(static_cast<float>(D));
+    const int64_t at0 = (static_cast<int64_t>(bh) * res_tokens + static_cast<int64_t>(chunk) * KT +
+                         wave * 16 + g4 * 4) * D + l16;
+    if (shared) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                unsafeAtomicAdd(dk + at0 + x * D + nb * 16, ak[nb][x] * ksc);
+                unsafeAtomicAdd(dv + at0 + x * D + nb * 16, av[nb][x]);
+            }
+    } else {
+        float ok[NB][4], ov[NB][4];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                ok[nb][x] = dk[at0 + x * D + nb * 16];
+                ov[nb][x] = dv[at0 + x * D + nb * 16];
+            }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                dk[at0 + x * D + nb * 16] = fmaf(ak[nb][x], ksc, ok[nb][x]);
+                dv[at0 + x * D + nb * 16] = ov[nb][x] + av[nb][x];
+            }
+    }
+}
+
+struct IndexShape {
+    int per, n_chunks, seg, cap_items, stride;
+    bool fits;
+};
+
+IndexShape index_shape(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
+    const hga_params& p = plan.p;
+    const int r = p.n_q_heads / p.n_kv_heads;
+    IndexShape s{};
+    const int64_t n_chunks = static_cast<int64_t>(q_chunk0) + n_q_chunks;
+    const int64_t fixed = 1 + VisibleChunks(static_cast<int>(n_chunks - 1), p.keep_first,
+                                            recent_window(p)).count;
+    const int64_t per = fixed + p.topk_groups;
+    const int64_t entries = per * n_q_chunks;
+    // Segments of at most 32 (unit, head) steps, shorter when that leaves
+    // fewer than about eight workgroups per compute unit.
+    const int64_t total = entries * p.batch * p.n_kv_heads;
+    int64_t seg = total / (static_cast<int64_t>(plan.n_cu) * 8);
+    const int64_t most = r >= 32 ? 1 : 32 / r;
+    seg = seg < 4 ? 4 : seg;
+    seg = seg > most ? most : seg;
+    const int64_t cap = n_chunks + entries / seg;
+    const int64_t stride = (2 * cap + entries + 3) / 4 * 4;
+    const int64_t rows = static_cast<int64_t>(r) * n_q_chunks * KT;  // per (batch, KV head)
+    // the row statistics and the tables live in dq
+    s.fits = n_chunks <= kBwdIndexChunks && stride + 2 * rows <= rows * p.head_dim &&
+             cap * p.batch * p.n_kv_heads <= (int64_t(1) << 24) && entries < (int64_t(1) << 30);
+    if (!s.fits) return s;
+    s.per = static_cast<int>(per);
+    s.n_chunks = static_cast<int>(n_chunks);
+    s.seg = static_cast<int>(seg);
+    s.cap_items = static_cast<int>(cap);
+    s.stride = static_cast<int>(stride);
+    return s;
+}
+
+template <int D, int QR, int NS>
+hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const void* q_rot,
+                           int q_chunk0, int n_q_chunks, const void* k_res, const void* v_res,
+                           int64_t res_tokens, const int32_t* group_idx, const void* dout,
+                           float* dq, float* dk, float* dv, hipStream_t stream) {
+    const hga_params& p = plan.p;
+    static std::atomic<uint64_t> configured{0};  // per instantiation and device
+    const hipError_t ce = once_per_device(configured, plan.device, [] {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_index_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 kBwdIndexChunks * 4);
+        if (e != hipSuccess) return e;
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_chunk_kernel<D, QR, NS>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   ChunkLayout<D, QR, NS>::kBytes);
+    });
+    if (ce != hipSuccess) return ce;
+    const int r = p.n_q_heads / p.n_kv_heads;
+    const int n_bh = p.batch * p.n_kv_heads;
+    const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
+    const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
+    const Index ix{reinterpret_cast<int*>(dq + 2 * rows), sh.stride, sh.cap_items};
+    hipLaunchKernelGGL(bwd_index_kernel, dim3(n_bh), dim3(kIndexThreads), sh.n_chunks * 4, stream,
+                       group_idx, n_q_chunks, q_chunk0, p.keep_first, recent_window(p),
+                       p.topk_groups, 6 - group_shift, FastDiv(sh.per), sh.n_chunks, sh.seg, ix);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int n_blocks = n_bh * sh.cap_items;
+    const int by_xcd = n_bh >= 2 * kXcds;
+    const int grid = by_xcd ? (n_blocks + kXcds - 1) / kXcds * kXcds : n_blocks;
+    hipLaunchKernelGGL((bwd_chunk_kernel<D, QR, NS>), dim3(grid), dim3(256), (ChunkLayout<D, QR, NS>::kBytes),
+                       stream, static_cast<const bf16_t*>(q_rot), q_chunk0, n_q_chunks,
+                       static_cast<const bf16_t*>(k_res), static_cast<const bf16_t*>(v_res),
+                       res_tokens, dq, static_cast<const bf16_t*>(dout), dk, dv, FastDiv(r),
+                       FastDiv(p.n_kv_heads), FastDiv(sh.cap_items), group_shift, ix, n_blocks,
+                       by_xcd);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool bwd_chunks_fit(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
+    return index_shape(plan, q_chunk0, n_q_chunks).fits;
+}
+
+size_t bwd_chunks_lds_bytes(const hga_plan& plan) {
+    const size_t stage = plan.p.head_dim == 64 ? ChunkLayout<64, 64, 2>::kBytes
+                                               : ChunkLayout<128, 32, 2>::kBytes;
+    return std::max<size_t>(stage, kBwdIndexChunks * 4 + 1024);
+}
+
+hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
+                             const void* k_res, const void* v_res, int64_t res_tokens,
+                             const int32_t* group_idx, const void* dout, float* dq, float* dk,
+                             float* dv, hipStream_t stream) {
+    const IndexShape sh = index_shape(plan, q_chunk0, n_q_chunks);
+    if (!sh.fits) return hipErrorInvalidConfiguration;
+    // d64: 64 query rows a step, four workgroups per CU; d128: 32, so that three fit
+    return (plan.p.head_dim == 64 ? launch_chunks_t<64, 64, 2> : launch_chunks_t<128, 32, 2>)(
+        plan, sh, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx, dout, dq, dk,
+        dv, stream);
+}
+
+}  // namespace hga

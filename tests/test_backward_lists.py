@@ -1,0 +1,110 @@
+"""The attention backward's chunk lists: group ids in any order, repeated,
+padded in the middle, in the causal future or inside an always-visible chunk;
+lists long enough to be cut (sinks); 8-, 16- and 32-token groups; a few query
+chunks after a long history, where the lists no longer fit the dq buffer; and
+gradients added to what dk and dv hold."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import hga_oracle as O
+from paper_2606_30709_amd import workloads as W
+
+from parity_util import BWD_TOL, f64
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(w, q0, gi, seed):
+    """Backward of the last chunks from q0 on for group ids gi, against the oracle."""
+    from paper_2606_30709_amd import hga
+    rng = np.random.default_rng(seed)
+    C, d, G = w.chunk, w.head_dim, w.group
+    n = w.n_chunks - q0
+    bf = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(torch.bfloat16)  # noqa: E731
+    q, dout = bf(w.batch, w.n_q_heads, n * C, d), bf(w.batch, w.n_q_heads, n * C, d)
+    k, v = bf(w.batch, w.n_kv_heads, w.seq_len, d), bf(w.batch, w.n_kv_heads, w.seq_len, d)
+    dev = [t.cuda() for t in (q, k, v, dout)]
+    plan = hga.Plan.for_workload(w)
+    out = torch.empty_like(dev[0])
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device="cuda")
+    ids = torch.from_numpy(gi.astype(np.int32)).cuda()
+    hga.hga_gather_attend(plan, dev[0], q0, dev[1], dev[2], ids, None, None, out, lse)
+    base = torch.from_numpy(rng.standard_normal(k.shape).astype(np.float32)).cuda()
+    dq = torch.full(q.shape, float("nan"), device="cuda")
+    dk, dv = base.clone(), -base
+    hga.hga_attend_backward(plan, dev[0], q0, dev[1], dev[2], ids, out, lse, dev[3], dq, dk, dv)
+    torch.cuda.synchronize()
+    valid = gi.copy()
+    for i in range(n):  # absent: outside the causal past
+        row = valid[:, :, i]
+        row[(row < 0) | (row >= (q0 + i) * (C // G))] = -1
+    x = [f64(t.view(torch.int16).numpy().view(np.uint16), "bf16") for t in (q, k, v, dout)]
+    ref = O.attend_backward(x[0], x[1], x[2], x[3], valid, list(range(q0, w.n_chunks)), C, G,
+                            w.keep_first, w.keep_last, w.force_prev)
+    b = base.cpu().double().numpy()
+    for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), (ref[0], ref[1] + b, ref[2] - b)):
+        err = np.abs(got.double().cpu().numpy() - want)
+        grad = want - (0 if name == "dq" else (b if name == "dk" else -b))
+        assert np.isfinite(err).all(), name
+        assert err.max() <= BWD_TOL * np.abs(grad).max(), name
+        assert np.linalg.norm(err) <= BWD_TOL / 4 * np.linalg.norm(grad), name
+
+
+def _ids(w, q0, rng):
+    """Random valid ids with repeats, then the odd ones the calls accept."""
+    n, gpc = w.n_chunks - q0, w.chunk // w.group
+    gi = np.full((w.batch, w.n_kv_heads, n, w.topk_groups), -1, dtype=np.int64)
+    for i in range(n):
+        c = q0 + i
+        if c > 1:
+            # ids of a few chunks, so that runs and repeats occur, any order
+            lo = int(rng.integers(0, max(1, c - 4)))
+            gi[:, :, i] = rng.integers(lo * gpc, min(c, lo + 4) * gpc, size=gi[:, :, i].shape)
+            if i % 3 == 0:
+                gi[:, :, i] = np.sort(gi[:, :, i], axis=-1)
+            if i % 4 == 1:
+                gi[:, :, i, w.topk_groups // 2] = -1
+            if i % 5 == 2:
+                gi[:, :, i, 0] = c * gpc       # the causal future
+    return gi
+
+
+@pytest.mark.parametrize("d,group,kv,ratio,kg,first,last", [
+    (64, 16, 3, 1, 12, 1, 0),
+    (64, 8, 1, 2, 21, 2, 3),
+    (64, 32, 2, 3, 5, 1, 1),
+    (64, 16, 1, 8, 7, 0, 2),
+    (128, 16, 2, 1, 9, 1, 2),
+    (128, 8, 1, 4, 13, 1, 0),
+    (128, 32, 1, 7, 4, 2, 1),
+    (128, 16, 1, 8, 6, 1, 1),     # unit by unit
+])
+def test_backward_group_id_forms(d, group, kv, ratio, kg, first, last):
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    w = W.preset("smalllm").with_(batch=1, n_q_heads=kv * ratio, n_kv_heads=kv, head_dim=d,
+                                  seq_len=64 * 21, group=group, topk_groups=kg, topk_chunks=4,
+                                  keep_first=first, keep_last=last, needle_mode="none")
+    rng = np.random.default_rng(d + group + kg)
+    for q0 in (0, 17):
+        _check(w, q0, _ids(w, q0, rng), seed=kg + q0)
+
+
+@pytest.mark.parametrize("d,chunks,q0", [
+    (64, 2050, 2049),    # the lists do not fit one query chunk's dq
+    (64, 2050, 2042),    # they fit eight's
+    (128, 70, 69),
+])
+def test_backward_few_query_chunks_after_a_long_history(d, chunks, q0):
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    w = W.preset("smalllm").with_(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=d,
+                                  seq_len=64 * chunks, topk_groups=12, topk_chunks=8,
+                                  needle_mode="none")
+    rng = np.random.default_rng(chunks + q0)
+    gi = np.sort(rng.integers(0, q0 * 4, size=(1, 1, chunks - q0, 12)), axis=-1)
+    _check(w, q0, gi, seed=q0)
