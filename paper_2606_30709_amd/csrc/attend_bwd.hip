@@ -29,6 +29,7 @@
 #include "attend_bwd.hpp"
 #include "attend_common.hpp"
 #include "hga_internal.hpp"
+#include "lds_copy.hpp"
 
 namespace hga {
 namespace {
@@ -41,10 +42,6 @@ constexpr int KT = 64;    // keys per tile (= chunk)
 
 __device__ __forceinline__ bf16x8_t frag(const bf16_t* p) {
     return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const vec16*>(p));
-}
-
-__device__ __forceinline__ bf16x4_t frag4(const bf16_t* p) {
-    return *reinterpret_cast<const bf16x4_t*>(p);
 }
 
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
@@ -64,26 +61,10 @@ __device__ __forceinline__ bf16x4_t k_tr4(const bf16_t* sk, int ks, int k0, int 
                                             (lds_i16x4_t*)(reinterpret_cast<uintptr_t>(p))));
 }
 
-// 16-bit element e of a 16-byte vector, and its value as a float when it is
-// a bf16 (taken from the 32-bit words: an element extracted from a bf16
-// vector type and stored on its own was seen to be miscompiled).
-__device__ __forceinline__ bf16_t elem16(const vec16& v, int e) {
-    return static_cast<bf16_t>(v.w[e >> 1] >> ((e & 1) * 16));
-}
-__device__ __forceinline__ float bf16_value(const vec16& v, int e) {
-    return __uint_as_float((e & 1) ? (v.w[e >> 1] & 0xffff0000u) : (v.w[e >> 1] << 16));
-}
-
 __device__ __forceinline__ float add_halves(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false,
                                                     false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Workgroup barrier that orders LDS only: waits for this wave's LDS
-// operations, not for its global atomics (which nothing here reads back).
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 constexpr int kXcds = 8;  // XCDs of the chip; workgroups are dealt to them in turn
@@ -112,217 +93,279 @@ __device__ __forceinline__ int tile_token(int tile, int row, int c, const Visibl
     return g >= 0 && g < lim ? (g << group_shift) + (rr & ((1 << group_shift) - 1)) : -1;
 }
 
-// dQ, query-major: a workgroup stages each key tile of a unit once for up to
-// eight 32-row query tiles, whose Q and dO fragments stay in registers.
+// dQ, query-major, on the forward's plan: 32-row query tiles, one wavefront
+// each (KS = 1) or two that take one 32-key half of every key tile and add up
+// at the end (KS = 2: one query head per KV head); a unit's key tiles (current
+// chunk, visible chunks, routed rows gathered by group id) stream through two
+// LDS stages, copied without registers.  Per 32-key sub-tile:
+//   S^T = K.Q^T, dP^T - D = V.dO^T - D  (A = rows from LDS, B = registers)
+//   dS^T = P (dP - D)                   (lane = query, registers = keys)
+//   dQ^T += K^T.dS^T                    (A = transpose reads of the K rows)
+// The contraction over keys is permuted alike in A and B, so dS goes from
+// accumulators to operand in registers.
+// Bound: vector work beside twelve (d64) matrix instructions per sub-tile and
+// wavefront, like the forward's.  Three wavefronts per SIMD at d64: held to
+// four it spills 9 VGPRs (8 x 12 heads x 12,288 tokens: 451 against 371 us; 9/3
+// heads x 2,880: 31 against 24).  Staging rows through registers and K a second
+// time, transposed by 16-bit writes, took 490 and 36 us there, and 1050
+// against 936 us on 32/4 heads of d128 x 32,768 tokens.
 template <int D>
 struct DqLayout {
-    static constexpr int KS = D + 8;
-    static constexpr int TS = KT + 4;
-    static constexpr int kK = 0;
-    static constexpr int kV = kK + KT * KS * 2;
-    static constexpr int kKT = kV + KT * KS * 2;
-    static constexpr int kTok = kKT + D * TS * 2;
-    static constexpr int kGid = kTok + KT * 4;
+    static constexpr int kRow = D * 2;
+    static constexpr int kTile = KT * kRow;         // K, then V
+    static constexpr int kStage = 2 * kTile;
+    static constexpr int kGid = 2 * kStage;
     static constexpr int kBytes = kGid + kMaxTopK * 4;
+    static constexpr int kOutRow = 36;              // floats: 32 dimensions, padded
+    static constexpr int kOut = 32 * kOutRow * 4;   // one wavefront's staging of the result
 };
 
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) void attend_bwd_dq_kernel(
+template <int D, int KS, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+void attend_bwd_dq_kernel(
     const bf16_t* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const bf16_t* __restrict__ k_res,
     const bf16_t* __restrict__ v_res, int64_t res_tokens, const int32_t* __restrict__ group_idx,
     const bf16_t* __restrict__ out, const float* __restrict__ lse,
-    const bf16_t* __restrict__ dout, float* __restrict__ dq, int r, int n_kv, int group_shift,
-    int keep_first, int window, int topk_groups, int wg_per_unit, int n_items) {
+    const bf16_t* __restrict__ dout, float* __restrict__ dq, int r, FastDiv kv_div, FastDiv wg_div,
+    FastDiv chunk_div, int group_shift, int keep_first, int window, int topk_groups, int n_items) {
     using Lay = DqLayout<D>;
-    constexpr int NKS = D / 16;
-    constexpr int NDT = D / 32;
-    constexpr int VPR = D / 8;
-    constexpr int TPR = NW * 64 / KT;  // staging threads per tile row
-    constexpr int VPT = VPR / TPR;     // 16-byte vectors per staging thread
-    static_assert(VPT >= 1 && VPT * TPR == VPR, "staging split");
+    constexpr int kRow = Lay::kRow;
+    constexpr int kRowShift = D == 64 ? 7 : 8;
+    constexpr int NKS = D / 16, NDT = D / 32;
+    constexpr int QT = NW / KS;                   // query tiles per workgroup
+    constexpr int KI = Lay::kTile / 1024 / NW;    // copies per wave and tile, for K (and V)
+    static_assert(KI >= 1, "copy split");
+    static_assert(KS == 1 || QT * (64 * NDT * 16 * 4 + Lay::kOut) <= Lay::kBytes, "merge area");
+    static_assert(KS == 2 || QT * Lay::kOut <= Lay::kBytes, "output staging area");
     extern __shared__ __align__(16) unsigned char smem[];
-    bf16_t* sK = reinterpret_cast<bf16_t*>(smem + Lay::kK);
-    bf16_t* sV = reinterpret_cast<bf16_t*>(smem + Lay::kV);
-    bf16_t* sKT = reinterpret_cast<bf16_t*>(smem + Lay::kKT);
-    int* s_tok = reinterpret_cast<int*>(smem + Lay::kTok);
-    int* s_gid = reinterpret_cast<int*>(smem + Lay::kGid);
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+    const int* s_gid = reinterpret_cast<const int*>(smem + Lay::kGid);
 
     const int item = xcd_item(n_items);
     if (item >= n_items) return;
-    const int unit = item / wg_per_unit, part = item % wg_per_unit;
-    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
-    const int b = bh / n_kv, j = bh % n_kv;
+    const int unit = wg_div.div(item), part = item - unit * wg_div.d;
+    const int bh = chunk_div.div(unit), i = unit - bh * n_q_chunks;
+    const int b = kv_div.div(bh), j = bh - b * kv_div.d;
     const int c = q_chunk0 + i;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
-    const int gpc = KT >> group_shift;
-    const int qtile = part * NW + wave;
+    const int qt_local = wave % QT, ksplit = wave / QT;
+    const int qtile = part * QT + qt_local;
     const bool qactive = qtile < 2 * r;
     const int routed_rows = topk_groups << group_shift;
-    const int64_t qtok = static_cast<int64_t>(n_q_chunks) * KT;
-    const int n_q_heads = r * n_kv;
-    auto qrow_of = [&](int m) {
-        const int row = (qactive ? qtile : 0) * 32 + m;
-        return (static_cast<int64_t>(b) * n_q_heads + j * r + row / KT) * qtok +
-               static_cast<int64_t>(i) * KT + row % KT;
-    };
-    const int t = (qtile * 32 + col) % KT;
-    const int64_t my_row = qrow_of(col);
+    const int lim = c * (KT >> group_shift);  // routed groups must lie in the causal past
     const float scale2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    const float inv_sqrt_d = 1.0f / sqrtf(static_cast<float>(D));
 
-    for (int s = tid; s < topk_groups; s += NW * 64)
-        s_gid[s] = group_idx[static_cast<int64_t>(unit) * topk_groups + s];
-
-    // B fragments of S^T = K.Q^T and dP^T = V.dO^T: the lane's query row,
-    // dimensions kk*16 + half*8 .. +7
-    bf16x8_t qf[NKS], gf[NKS];
-    float dsum = 0.f, lse2 = 0.f;
+    const u32x4 rk = rsrc_words(k_res + static_cast<int64_t>(bh) * res_tokens * D,
+                                static_cast<uint32_t>(res_tokens * kRow));
+    const u32x4 rv = rsrc_words(v_res + static_cast<int64_t>(bh) * res_tokens * D,
+                                static_cast<uint32_t>(res_tokens * kRow));
     {
-        float acc = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < NKS; ++kk) {
-            qf[kk] = bf16x8_t{};
-            gf[kk] = bf16x8_t{};
-            if (qactive) {
-                qf[kk] = frag(q_rot + my_row * D + kk * 16 + half * 8);
-                gf[kk] = frag(dout + my_row * D + kk * 16 + half * 8);
-                const bf16x8_t o8 = frag(out + my_row * D + kk * 16 + half * 8);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    acc = fmaf(static_cast<float>(gf[kk][e]), static_cast<float>(o8[e]), acc);
-            }
-        }
-        dsum = add_halves(acc);
-        if (qactive) lse2 = lse[my_row] * 1.4426950408889634f;
+        const u32x4 rg = rsrc_words(group_idx + static_cast<int64_t>(unit) * topk_groups, topk_groups * 4);
+        for (int u = wave; u * 64 < topk_groups; u += NW)
+            copy4_to_lds(rg, (u * 64 + lane) * 4, lds0 + Lay::kGid + u * 256);
     }
 
-    f32x16_t dqacc[NDT];
+    // the tile's first query row; B operands: the lane's row of Q and dO,
+    // dimensions kk*16 + half*8 .. +7
+    const int row_in_unit = (qactive ? qtile : 0) * 32;
+    const int64_t row0 = (static_cast<int64_t>(b) * (r * kv_div.d) + j * r + row_in_unit / KT) *
+                             (static_cast<int64_t>(n_q_chunks) * KT) +
+                         static_cast<int64_t>(i) * KT + row_in_unit % KT;
+    const int tq = qtile & 1;  // half of the chunk the tile's tokens lie in
+    bf16x8_t qf[NKS], gf[NKS];
+    float nd = 0.f, nl = 0.f;  // -D_i, -lse (log2)
+    {
+        const int64_t at = (row0 + col) * D + half * 8;
 #pragma unroll
-    for (int nb = 0; nb < NDT; ++nb)
+        for (int kk = 0; kk < NKS; ++kk) {
+            const vec16 g = load16(dout + at + kk * 16), o = load16(out + at + kk * 16);
+            qf[kk] = frag(q_rot + at + kk * 16);
+            gf[kk] = __builtin_bit_cast(bf16x8_t, g);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dqacc[nb][e] = 0.f;
+            for (int e = 0; e < 8; ++e) nd = fmaf(-bf16_value(g, e), bf16_value(o, e), nd);
+        }
+        nd = add_halves(nd);
+        nl = lse[row0 + col] * -1.4426950408889634f;
+    }
 
     const VisibleChunks vis(c, keep_first, window);
-    const int n_tiles = 1 + vis.count + (routed_rows + KT - 1) / KT;
-    const bf16_t* kbase = k_res + static_cast<int64_t>(bh) * res_tokens * D;
-    const bf16_t* vbase = v_res + static_cast<int64_t>(bh) * res_tokens * D;
-    const int lim = c * gpc;
-
-    // The next tile's rows are fetched into registers while this one is
-    // used.  K is also staged transposed (K^T rows, one 16-bit write per
-    // element): the eight query-tile waves all read K^T for dQ, so one copy
-    // per tile costs less than a transpose read per wave (measured).
-    const int srow = tid % KT, pv = tid / KT;
-    vec16 kx[VPT], vx[VPT];
-    int stok = -1;
-    auto fetch = [&](int tile) {
-        stok = tile_token(tile, srow, c, vis, s_gid, routed_rows, group_shift, lim);
+    const int n_vis = vis.count;
+    const int n_tiles = 1 + n_vis + (routed_rows + KT - 1) / KT;
+    uint32_t koff[KI];  // this lane's source offset in each copy of a tile
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) {
-            const int cv = pv * VPT + u;
-            kx[u] = vec16{{0u, 0u, 0u, 0u}};
-            vx[u] = kx[u];
-            if (stok >= 0) {
-                kx[u] = load16(kbase + static_cast<int64_t>(stok) * D + cv * 8);
-                vx[u] = load16(vbase + static_cast<int64_t>(stok) * D + cv * 8);
+    for (int u = 0; u < KI; ++u) {
+        const int slot = (u * NW + wave) * 64 + lane, row = slot / (D / 8);
+        koff[u] = row * kRow + ((slot % (D / 8)) ^ swz<D>(row)) * 16;
+    }
+    auto issue = [&](int tile, int stage) {
+        uint32_t src[KI];
+        if (tile <= n_vis) {
+            const uint32_t base = static_cast<uint32_t>((tile == 0 ? c : vis.chunk(tile - 1)) * Lay::kTile);
+#pragma unroll
+            for (int u = 0; u < KI; ++u) src[u] = base + koff[u];
+        } else {
+            // row R of the tile is row R % G of the group in slot R / G
+            const int slot0 = ((tile - 1 - n_vis) * KT) >> group_shift;
+            const int sh = group_shift + kRowShift;
+            int g[KI];
+#pragma unroll
+            for (int u = 0; u < KI; ++u)
+                g[u] = s_gid[min(slot0 + static_cast<int>(koff[u] >> sh), topk_groups - 1)];
+#pragma unroll
+            for (int u = 0; u < KI; ++u) {
+                const bool ok = slot0 + static_cast<int>(koff[u] >> sh) < topk_groups &&
+                                static_cast<uint32_t>(g[u]) < static_cast<uint32_t>(lim);
+                src[u] = ok ? (static_cast<uint32_t>(g[u]) << sh) + (koff[u] & ((1u << sh) - 1)) : kAbsent;
             }
         }
+        const uint32_t at = lds0 + stage * Lay::kStage;
+#pragma unroll
+        for (int u = 0; u < KI; ++u) copy16_to_lds(rk, src[u], at + (u * NW + wave) * 1024);
+#pragma unroll
+        for (int u = 0; u < KI; ++u) copy16_to_lds(rv, src[u], at + Lay::kTile + (u * NW + wave) * 1024);
     };
-    fetch(0);  // the current chunk: no group id needed yet
+    issue(0, 0);
+
+    f32x16_t acc[NDT];  // dQ^T: lane = query, dimension dt*32 + (e/4)*8 + half*4 + e%4
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
+    // LDS offsets of this lane's reads; the swizzle repeats every 16 rows, so
+    // rows further on are immediates
+    int aoff[NKS], toff[2][NDT];
+#pragma unroll
+    for (int kk = 0; kk < NKS; ++kk) aoff[kk] = col * kRow + (((2 * kk + half) ^ swz<D>(col)) * 16);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+            const int row = x * 8 + half * 4 + ((lane & 15) >> 2);
+            const int ch = dt * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+            toff[x][dt] = row * kRow + ((ch ^ swz<D>(row)) * 16) + (lane & 1) * 8;
+        }
 
     for (int tile = 0; tile < n_tiles; ++tile) {
-        if (tile > 0) lds_barrier();  // every wave is done with the previous tile
-        if (pv == 0) s_tok[srow] = stok;
-#pragma unroll
-        for (int u = 0; u < VPT; ++u) {
-            const int cv = pv * VPT + u;
-            *reinterpret_cast<vec16*>(sK + srow * Lay::KS + cv * 8) = kx[u];
-            *reinterpret_cast<vec16*>(sV + srow * Lay::KS + cv * 8) = vx[u];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sKT[(cv * 8 + e) * Lay::TS + srow] = elem16(kx[u], e);
-        }
-        lds_barrier();
-        if (tile + 1 < n_tiles) fetch(tile + 1);
+        wait_copies<0>();
+        lds_barrier();  // the tile is here; everybody has left the other stage
+        if (tile + 1 < n_tiles) issue(tile + 1, (tile + 1) & 1);
         if (!qactive) continue;
-        const bool current = tile == 0;
+        const unsigned char* base = smem + (tile & 1) * Lay::kStage;
+        // routed rows to leave out: lane g checks the tile's g-th group
+        bool partial = false;
+        const int rt0 = (tile - 1 - n_vis) * KT;
+        if (tile > n_vis) {
+            bool bad = false;
+            if (lane < (KT >> group_shift)) {
+                const int g = (rt0 >> group_shift) + lane;
+                bad = g >= topk_groups || static_cast<uint32_t>(s_gid[min(g, topk_groups - 1)]) >=
+                                              static_cast<uint32_t>(lim);
+            }
+            partial = __builtin_amdgcn_ballot_w64(bad) != 0;
+        }
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            f32x16_t sacc, pacc;
+        for (int x = 0; x < 2 / KS; ++x) {
+            const int st = KS == 2 ? ksplit : x;
+            if (tile == 0 && st > tq) continue;  // the later half of the current chunk
+            const unsigned char* kb = base + st * 32 * kRow;
+            f32x16_t s, p;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                sacc[e] = 0.f;
-                pacc[e] = 0.f;
+                s[e] = 0.f;
+                p[e] = nd;
             }
-            const int krow = st * 32 + col;
 #pragma unroll
             for (int kk = 0; kk < NKS; ++kk) {
-                const int off = kk * 16 + half * 8;
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(sK + krow * Lay::KS + off), qf[kk],
-                                                               sacc, 0, 0, 0);
-                pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(sV + krow * Lay::KS + off), gf[kk],
-                                                               pacc, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8_t, load16(kb + aoff[kk])), qf[kk], s, 0, 0, 0);
+                p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8_t, load16(kb + Lay::kTile + aoff[kk])), gf[kk], p, 0, 0, 0);
             }
-            bf16x8_t dsf[2];
+            if (tile == 0 && st == tq) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int key = st * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-                const bool ok = s_tok[key] >= 0 && (!current || key <= t);
-                const float p = __builtin_amdgcn_exp2f(ok ? sacc[e] * scale2 - lse2 : -INFINITY);
-                dsf[e >> 3][e & 7] = static_cast<__bf16>(p * (pacc[e] - dsum));
+                for (int e = 0; e < 16; ++e)
+                    s[e] = (e >> 2) * 8 + half * 4 + (e & 3) > col ? -INFINITY : s[e];
+            } else if (partial) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int g = (rt0 + st * 32 + (e >> 2) * 8 + half * 4 + (e & 3)) >> group_shift;
+                    const bool ok = g < topk_groups && static_cast<uint32_t>(s_gid[min(g, topk_groups - 1)]) <
+                                                           static_cast<uint32_t>(lim);
+                    s[e] = ok ? s[e] : -INFINITY;
+                }
             }
+            bf16x8_t ds[2];
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                ds[e >> 3][e & 7] = static_cast<__bf16>(
+                    __builtin_amdgcn_exp2f(fmaf(s[e], scale2, nl)) * p[e]);
+            // k-slot half*8 + e of block kap is key kap*16 + (e/4)*8 + half*4 + e%4
 #pragma unroll
             for (int kap = 0; kap < 2; ++kap)
 #pragma unroll
-                for (int nb = 0; nb < NDT; ++nb) {
-                    const bf16_t* kp = sKT + (nb * 32 + col) * Lay::TS + st * 32 + kap * 16 + half * 4;
-                    const bf16x8_t bf = __builtin_shufflevector(frag4(kp), frag4(kp + 8), 0, 1, 2, 3, 4, 5, 6, 7);
-                    dqacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[kap], bf, dqacc[nb], 0, 0, 0);
+                for (int dt = 0; dt < NDT; ++dt) {
+                    auto tr = [&](int off) {
+                        return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                            (lds_i16x4_t*)(reinterpret_cast<uintptr_t>(kb + kap * 16 * kRow + off)));
+                    };
+                    const bf16x8_t a = __builtin_bit_cast(
+                        bf16x8_t, __builtin_shufflevector(tr(toff[0][dt]), tr(toff[1][dt]), 0, 1, 2, 3, 4, 5, 6, 7));
+                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, ds[kap], acc[dt], 0, 0, 0);
                 }
         }
     }
 
-    if (qactive) {
+    lds_barrier();  // the stages are free
+    float* stage = reinterpret_cast<float*>(smem + qt_local * Lay::kOut);
+    if (KS == 2) {
+        float* other = reinterpret_cast<float*>(smem + QT * Lay::kOut) + qt_local * (NDT * 16 * 64) + lane;
+        if (ksplit == 1) {
 #pragma unroll
-        for (int nb = 0; nb < NDT; ++nb)
+            for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int m = (e >> 2) * 8 + half * 4 + (e & 3);
-                dq[qrow_of(m) * D + nb * 32 + col] = dqacc[nb][e] * inv_sqrt_d;
-            }
+                for (int e = 0; e < 16; ++e) other[(dt * 16 + e) * 64] = acc[dt][e];
+        }
+        lds_barrier();
+        if (ksplit == 1) return;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[dt][e] += other[(dt * 16 + e) * 64];
+    }
+    if (!qactive) return;
+    // 32 dimensions at a time through the wavefront's LDS rows, so that every
+    // store instruction writes whole 128-byte pieces of eight rows
+    const float inv_sqrt_d = 1.0f / sqrtf(static_cast<float>(D));
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4*>(stage + col * Lay::kOutRow + g * 8 + half * 4) =
+                make_float4(acc[dt][g * 4] * inv_sqrt_d, acc[dt][g * 4 + 1] * inv_sqrt_d,
+                            acc[dt][g * 4 + 2] * inv_sqrt_d, acc[dt][g * 4 + 3] * inv_sqrt_d);
+        __builtin_amdgcn_wave_barrier();
+        lds_reads_done();  // (writes too: the wavefront's own)
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int row = it * 8 + (lane >> 3), cc = lane & 7;
+            const vec16 x = *reinterpret_cast<const vec16*>(stage + row * Lay::kOutRow + cc * 4);
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, x),
+                                        reinterpret_cast<u32x4*>(dq + (row0 + row) * D + dt * 32 + cc * 4));
+        }
+        __builtin_amdgcn_wave_barrier();
+        lds_reads_done();
     }
 }
 
-// Row statistics: per 32 query rows (in lse's order), their 32 values of -lse
-// in log2 units, then their 32 of -D_i = -dout_i . out_i.  Eight lanes per
-// row, each over every eighth 16-byte vector.
 template <int D>
 __global__ __launch_bounds__(256) void attend_bwd_stat_kernel(const bf16_t* __restrict__ out,
                                                               const bf16_t* __restrict__ dout,
                                                               const float* __restrict__ lse,
                                                               float* __restrict__ stat, int64_t rows) {
-    constexpr int VPR = D / 8;
-    const int64_t row = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) >> 3;
-    const int part = threadIdx.x & 7;
-    float acc = 0.f;
-    if (row < rows) {
-#pragma unroll
-        for (int u = 0; u < VPR / 8; ++u) {
-            const vec16 g = load16(dout + row * D + (u * 8 + part) * 8);
-            const vec16 o = load16(out + row * D + (u * 8 + part) * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc = fmaf(bf16_value(g, e), bf16_value(o, e), acc);
-        }
-    }
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
-    acc += __shfl_xor(acc, 4);
-    if (row < rows && part == 0) {
-        float* at = stat + (row >> 5) * 64 + (row & 31);
-        at[0] = lse[row] * -1.4426950408889634f;
-        at[32] = -acc;
-    }
+    bwd_row_stat<D>(out, dout, lse, stat, rows,
+                    static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x);
 }
 
 // dK, dV key-major within a unit.  Work item (unit, tile group): 2*NSUB
@@ -576,13 +619,17 @@ __global__ __launch_bounds__(NSUB * 128) __attribute__((amdgpu_waves_per_eu(2, 2
 // heads 785 / 456 and 1733 / 863, 4 heads 518 / 420 and 1032 / 806, 6 heads
 // 445 / 440 and 892 / 845, 8 heads 517 / 525 and 979 / 1056 (and 32,768
 // tokens, where every unit's rows no longer come from the L2, 3150 / 3500).
+// At d128 and fewer than 32 units the lists' launch is not won back (2 heads x
+// 20 chunks: 46 / 50, x 50 chunks: 87 / 78).
 bool by_chunk(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
-    return (p.head_dim == 64 || r < 8) && bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
+    const int64_t units = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks;
+    return (p.head_dim == 64 || r == 1 || (r < 8 && units >= 32)) &&
+           bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
 }
 
-template <int D, int kNwDq>
+template <int D, int KS, int NW>
 hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                         const void* k_res, const void* v_res, int64_t res_tokens,
                         const int32_t* group_idx, const void* out, const float* lse,
@@ -592,7 +639,7 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
         const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&attend_bwd_dq_kernel<D, kNwDq>),
+            reinterpret_cast<const void*>(&attend_bwd_dq_kernel<D, KS, NW>),
             hipFuncAttributeMaxDynamicSharedMemorySize, DqLayout<D>::kBytes);
         if (e != hipSuccess) return e;
         return hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bwd_kv_kernel<D, kSub>),
@@ -603,7 +650,7 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
     const int window = recent_window(p);
     const int64_t units = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks;
-    const int wg_per_unit = (2 * r + kNwDq - 1) / kNwDq;
+    const int wg_per_unit = (2 * r * KS + NW - 1) / NW;
     // tiles of the largest working set: the last chunk's visible chunks
     const int c_max = q_chunk0 + n_q_chunks - 1;
     const int n_rt = (p.topk_groups * p.group + KT - 1) / KT;
@@ -616,15 +663,17 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     // (last) overwrites: no workspace of its own.
     const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
     float* stat = dq;
-    hipLaunchKernelGGL((attend_bwd_stat_kernel<D>), dim3(static_cast<unsigned>((rows * 8 + 255) / 256)),
-                       dim3(256), 0, stream, static_cast<const bf16_t*>(out),
-                       static_cast<const bf16_t*>(dout), lse, stat, rows);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipError_t e;
     if (by_chunk(plan, q_chunk0, n_q_chunks)) {
         e = launch_bwd_chunks(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                              group_idx, dout, dq, dk, dv, stream);
+                              group_idx, out, lse, dout, dq, dk, dv, stream);
     } else {
+        hipLaunchKernelGGL((attend_bwd_stat_kernel<D>),
+                           dim3(static_cast<unsigned>((rows * 8 + 255) / 256)), dim3(256), 0,
+                           stream, static_cast<const bf16_t*>(out),
+                           static_cast<const bf16_t*>(dout), lse, stat, rows);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL((attend_bwd_kv_kernel<D, kSub>), grid(items_kv), dim3(kSub * 128),
                            KvLayout<D>::kBytes, stream, static_cast<const bf16_t*>(q_rot),
                            q_chunk0, n_q_chunks, static_cast<const bf16_t*>(k_res),
@@ -634,12 +683,13 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attend_bwd_dq_kernel<D, kNwDq>), grid(items_dq), dim3(kNwDq * 64),
+    hipLaunchKernelGGL((attend_bwd_dq_kernel<D, KS, NW>), grid(items_dq), dim3(NW * 64),
                        DqLayout<D>::kBytes, stream, static_cast<const bf16_t*>(q_rot), q_chunk0,
                        n_q_chunks, static_cast<const bf16_t*>(k_res), static_cast<const bf16_t*>(v_res),
                        res_tokens, group_idx, static_cast<const bf16_t*>(out), lse,
-                       static_cast<const bf16_t*>(dout), dq, r, p.n_kv_heads, group_shift, p.keep_first,
-                       window, p.topk_groups, wg_per_unit, static_cast<int>(items_dq));
+                       static_cast<const bf16_t*>(dout), dq, r, FastDiv(p.n_kv_heads),
+                       FastDiv(wg_per_unit), FastDiv(n_q_chunks), group_shift, p.keep_first,
+                       window, p.topk_groups, static_cast<int>(items_dq));
     return hipGetLastError();
 }
 
@@ -658,18 +708,16 @@ hipError_t launch_attend_backward(const hga_plan& plan, const void* q_rot, int q
                                   float* dv, hipStream_t stream) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
-#define HGA_BWD(DD, NN)                                                                         \
-    return launch_bwd_t<DD, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,   \
-                                group_idx, out, lse, dout, dq, dk, dv, stream)
-    // the dq kernel's wavefronts: one per 32-row query tile, up to eight
+#define HGA_BWD(DD, KK, NN)                                                                        \
+    return launch_bwd_t<DD, KK, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,  \
+                                    group_idx, out, lse, dout, dq, dk, dv, stream)
+    // the dq kernel's shape: the forward's
     if (p.head_dim == 64) {
-        if (r == 1) HGA_BWD(64, 2);
-        if (r == 2) HGA_BWD(64, 4);
-        HGA_BWD(64, 8);
+        if (r == 1) HGA_BWD(64, 2, 4);
+        HGA_BWD(64, 1, 4);
     }
-    if (r == 1) HGA_BWD(128, 2);
-    if (r == 2) HGA_BWD(128, 4);
-    HGA_BWD(128, 8);
+    if (r == 1) HGA_BWD(128, 2, 4);
+    HGA_BWD(128, 1, 8);
 #undef HGA_BWD
 }
 

@@ -12,7 +12,8 @@
 //   bwd_index_kernel      one workgroup per (batch, KV head) counts, scans
 //                         and fills, per key chunk, the list of (query unit,
 //                         opened groups) entries, and cuts long lists (sink
-//                         chunks, chunks everybody looks up) into segments.
+//                         chunks, chunks everybody looks up) into segments;
+//                         the others compute the row statistics.
 //   bwd_chunk_kernel      one workgroup per segment.
 //
 // Both keep their tables in the caller's dq buffer, which the dQ kernel
@@ -102,11 +103,20 @@ __device__ __forceinline__ void each_entry(const int32_t* __restrict__ gid, int 
     }
 }
 
-// Bound by its two passes over the ids and the LDS counters: a few
-// microseconds beside the kernels it feeds.
+// The lists and the row statistics in one launch (neither needs the other):
+// the first n_bh workgroups invert one (batch, KV head) each, bound by their
+// two passes over its ids, while the others stream out and dout.
+template <int D>
 __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
     const int32_t* __restrict__ group_idx, int nq, int q_chunk0, int keep_first, int window,
-    int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, Index ix) {
+    int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, Index ix, int n_bh,
+    const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
+    const float* __restrict__ lse, float* __restrict__ stat, int64_t rows) {
+    if (blockIdx.x >= n_bh) {
+        bwd_row_stat<D>(out, dout, lse, stat, rows,
+                        (static_cast<int64_t>(blockIdx.x) - n_bh) * kIndexThreads + threadIdx.x);
+        return;
+    }
     extern __shared__ int s_cnt[];  // [n_chunks]
     __shared__ int s_sum[2][kIndexThreads / 64];
     const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -155,19 +165,6 @@ __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
                [&](int chunk, uint32_t e) { entries[atomicAdd(&s_cnt[chunk], 1)] = e; });
 }
 
-// 16-byte chunk j of staged row r is stored at j ^ swz(r).  The 16-byte
-// fragment reads of 16 consecutive rows then fall in distinct banks, and so
-// do the transpose reads, whose 32 bytes per row come from rows 0..7 or from
-// rows 0..3 and 8..11 of a 16-row block in one cycle.
-template <int D>
-__device__ __forceinline__ int swz(int r) {
-    if constexpr (D == 64)  // two rows span the banks: r >> 1 counts
-        return (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) | ((r >> 3) & 1);
-    else
-        return ((r & 1) << 3) | (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) |
-               ((r >> 3) & 1);
-}
-
 // QR query rows per step, NS steps in the LDS ring.
 template <int D, int QR, int NS>
 struct ChunkLayout {
@@ -177,10 +174,6 @@ struct ChunkLayout {
     static constexpr int kStage = kStat + QR / 32 * 256;
     static constexpr int kBytes = NS * kStage;
 };
-
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // One segment: the chunk's 64 keys, 16 to a wavefront (K and V fragments, dK
 // and dV in registers), against the segment's (unit, query head) pairs, 64
@@ -432,11 +425,14 @@ IndexShape index_shape(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
     const int64_t per = fixed + p.topk_groups;
     const int64_t entries = per * n_q_chunks;
     // Segments of at most 32 (unit, head) steps, shorter when that leaves
-    // fewer than about eight workgroups per compute unit.
+    // fewer than about eight workgroups per compute unit, but of about four:
+    // shorter ones only add atomics (one head x 100 chunks, K_g 40: 61 us at
+    // four steps, 66 at one; six heads x 20 chunks, 62 at 24 steps, 41 at six).
     const int64_t total = entries * p.batch * p.n_kv_heads;
     int64_t seg = total / (static_cast<int64_t>(plan.n_cu) * 8);
     const int64_t most = r >= 32 ? 1 : 32 / r;
-    seg = seg < 4 ? 4 : seg;
+    const int64_t least = r >= 4 ? 1 : 4 / r;
+    seg = seg < least ? least : seg;
     seg = seg > most ? most : seg;
     const int64_t cap = n_chunks + entries / seg;
     const int64_t stride = (2 * cap + entries + 3) / 4 * 4;
@@ -456,12 +452,13 @@ IndexShape index_shape(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
 template <int D, int QR, int NS>
 hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const void* q_rot,
                            int q_chunk0, int n_q_chunks, const void* k_res, const void* v_res,
-                           int64_t res_tokens, const int32_t* group_idx, const void* dout,
-                           float* dq, float* dk, float* dv, hipStream_t stream) {
+                           int64_t res_tokens, const int32_t* group_idx, const void* out,
+                           const float* lse, const void* dout, float* dq, float* dk, float* dv,
+                           hipStream_t stream) {
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_index_kernel),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_index_kernel<D>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  kBwdIndexChunks * 4);
         if (e != hipSuccess) return e;
@@ -475,9 +472,12 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
     const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
     const Index ix{reinterpret_cast<int*>(dq + 2 * rows), sh.stride, sh.cap_items};
-    hipLaunchKernelGGL(bwd_index_kernel, dim3(n_bh), dim3(kIndexThreads), sh.n_chunks * 4, stream,
-                       group_idx, n_q_chunks, q_chunk0, p.keep_first, recent_window(p),
-                       p.topk_groups, 6 - group_shift, FastDiv(sh.per), sh.n_chunks, sh.seg, ix);
+    const unsigned stat_blocks = static_cast<unsigned>((rows * 8 + kIndexThreads - 1) / kIndexThreads);
+    hipLaunchKernelGGL((bwd_index_kernel<D>), dim3(n_bh + stat_blocks), dim3(kIndexThreads),
+                       sh.n_chunks * 4, stream, group_idx, n_q_chunks, q_chunk0, p.keep_first,
+                       recent_window(p), p.topk_groups, 6 - group_shift, FastDiv(sh.per),
+                       sh.n_chunks, sh.seg, ix, n_bh, static_cast<const bf16_t*>(out),
+                       static_cast<const bf16_t*>(dout), lse, dq, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int n_blocks = n_bh * sh.cap_items;
@@ -506,14 +506,15 @@ size_t bwd_chunks_lds_bytes(const hga_plan& plan) {
 
 hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                              const void* k_res, const void* v_res, int64_t res_tokens,
-                             const int32_t* group_idx, const void* dout, float* dq, float* dk,
-                             float* dv, hipStream_t stream) {
+                             const int32_t* group_idx, const void* out, const float* lse,
+                             const void* dout, float* dq, float* dk, float* dv,
+                             hipStream_t stream) {
     const IndexShape sh = index_shape(plan, q_chunk0, n_q_chunks);
     if (!sh.fits) return hipErrorInvalidConfiguration;
     // d64: 64 query rows a step, four workgroups per CU; d128: 32, so that three fit
     return (plan.p.head_dim == 64 ? launch_chunks_t<64, 64, 2> : launch_chunks_t<128, 32, 2>)(
-        plan, sh, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx, dout, dq, dk,
-        dv, stream);
+        plan, sh, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx, out, lse,
+        dout, dq, dk, dv, stream);
 }
 
 }  // namespace hga
