@@ -711,12 +711,18 @@ hipError_t launch_attend_backward(const hga_plan& plan, const void* q_rot, int q
 #define HGA_BWD(DD, KK, NN)                                                                        \
     return launch_bwd_t<DD, KK, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,  \
                                     group_idx, out, lse, dout, dq, dk, dv, stream)
-    // the dq kernel's shape: the forward's
-    if (p.head_dim == 64) {
-        if (r == 1) HGA_BWD(64, 2, 4);
-        HGA_BWD(64, 1, 4);
+    // The dq kernel's shape: two wavefronts per query tile for one query head
+    // per KV head (two tiles a unit), and where one wavefront per tile would
+    // leave compute units without a workgroup (whole backward, one KV head: 2
+    // heads x 20 chunks of d64 33 -> 30 us, 4 x 50 66 -> 55, 4 x 100 of d128
+    // 101 -> 85; at 200 workgroups of d128 equal).
+    const int64_t units = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks;
+    const int tiles = p.head_dim == 64 ? 4 : 8;  // per workgroup, one wavefront each
+    if (r == 1 || units * ((2 * r + tiles - 1) / tiles) < plan.n_cu) {
+        if (p.head_dim == 64) HGA_BWD(64, 2, 4);
+        HGA_BWD(128, 2, 4);
     }
-    if (r == 1) HGA_BWD(128, 2, 4);
+    if (p.head_dim == 64) HGA_BWD(64, 1, 4);
     HGA_BWD(128, 1, 8);
 #undef HGA_BWD
 }
