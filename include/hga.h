@@ -419,6 +419,19 @@ hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t 
                                const float* lse, const void* dout, float* dq, float* dk,
                                float* dv, void* stream);
 
+/* hga_attend_backward for a caller with no gradients to add to: dk and dv are
+ * WRITTEN over all res_tokens rows (zeros where no query chunk of the call
+ * attends) and need not hold anything before.  The same sums as
+ * hga_attend_backward into zeros, without reading them and without the
+ * caller's zeroing.  dk and dv must not overlap each other or any other
+ * argument.  Other arguments, requirements and errors as
+ * hga_attend_backward. */
+hga_status hga_attend_backward_write(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
+                                     int32_t n_q_chunks, const void* k_res, const void* v_res,
+                                     int64_t res_tokens, const int32_t* group_idx,
+                                     const void* out, const float* lse, const void* dout,
+                                     float* dq, float* dk, float* dv, void* stream);
+
 /* hga_gather_kv followed by hga_attend_split, as one pass, for any layout
  * (Sec. 4.3 gather, Sec. 3.4 attention): the workgroups of a unit's routed
  * tiles copy the routed groups' rows straight from k_src/v_src (rows

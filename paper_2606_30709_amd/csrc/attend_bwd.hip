@@ -359,6 +359,16 @@ void attend_bwd_dq_kernel(
     }
 }
 
+// Zeros over n 16-byte vectors of dk and of dv (a kernel, not a memset: the
+// call may be captured into a graph).
+__global__ __launch_bounds__(256) void bwd_zero_kernel(float4* __restrict__ dk,
+                                                       float4* __restrict__ dv, int64_t n) {
+    const int64_t at = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (at + u * 256 < n) dk[at + u * 256] = dv[at + u * 256] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void attend_bwd_stat_kernel(const bf16_t* __restrict__ out,
                                                               const bf16_t* __restrict__ dout,
@@ -633,7 +643,8 @@ template <int D, int KS, int NW>
 hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                         const void* k_res, const void* v_res, int64_t res_tokens,
                         const int32_t* group_idx, const void* out, const float* lse,
-                        const void* dout, float* dq, float* dk, float* dv, hipStream_t stream) {
+                        const void* dout, float* dq, float* dk, float* dv, bool write,
+                        hipStream_t stream) {
     const hga_params& p = plan.p;
     constexpr int kSub = 2;  // 32-key sub-tiles per key-side workgroup (one tile)
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
@@ -666,8 +677,16 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     hipError_t e;
     if (by_chunk(plan, q_chunk0, n_q_chunks)) {
         e = launch_bwd_chunks(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                              group_idx, out, lse, dout, dq, dk, dv, stream);
+                              group_idx, out, lse, dout, dq, dk, dv, write, stream);
     } else {
+        if (write) {
+            const int64_t n = static_cast<int64_t>(p.batch) * p.n_kv_heads * res_tokens * (D / 4);
+            hipLaunchKernelGGL(bwd_zero_kernel, dim3(static_cast<unsigned>((n + 1023) / 1024)),
+                               dim3(256), 0, stream, reinterpret_cast<float4*>(dk),
+                               reinterpret_cast<float4*>(dv), n);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL((attend_bwd_stat_kernel<D>),
                            dim3(static_cast<unsigned>((rows * 8 + 255) / 256)), dim3(256), 0,
                            stream, static_cast<const bf16_t*>(out),
@@ -705,12 +724,12 @@ hipError_t launch_attend_backward(const hga_plan& plan, const void* q_rot, int q
                                   int n_q_chunks, const void* k_res, const void* v_res,
                                   int64_t res_tokens, const int32_t* group_idx, const void* out,
                                   const float* lse, const void* dout, float* dq, float* dk,
-                                  float* dv, hipStream_t stream) {
+                                  float* dv, bool write, hipStream_t stream) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
 #define HGA_BWD(DD, KK, NN)                                                                        \
     return launch_bwd_t<DD, KK, NN>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,  \
-                                    group_idx, out, lse, dout, dq, dk, dv, stream)
+                                    group_idx, out, lse, dout, dq, dk, dv, write, stream)
     // The dq kernel's shape: two wavefronts per query tile for one query head
     // per KV head (two tiles a unit), and where one wavefront per tile would
     // leave compute units without a workgroup (whole backward, one KV head: 2

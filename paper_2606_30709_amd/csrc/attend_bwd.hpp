@@ -16,12 +16,13 @@ constexpr int kBwdIndexChunks = 16384;
 bool bwd_chunks_fit(const hga_plan& plan, int q_chunk0, int n_q_chunks);
 size_t bwd_chunks_lds_bytes(const hga_plan& plan);
 
-// dk += .., dv += .. for the query chunks' attention.  dq is scratch: the row
-// statistics (bwd_row_stat), then the lists.
+// dk += .., dv += .. for the query chunks' attention (or `write`: = .., and
+// zeros in the other rows).  dq is scratch: the row statistics
+// (bwd_row_stat), then the lists.
 hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* group_idx, const void* out, const float* lse,
-                             const void* dout, float* dq, float* dk, float* dv,
+                             const void* dout, float* dq, float* dk, float* dv, bool write,
                              hipStream_t stream);
 
 // 16-byte chunk j of staged row r is stored at j ^ swz(r).  The 16-byte

@@ -110,7 +110,7 @@ template <int D>
 __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
     const int32_t* __restrict__ group_idx, int nq, int q_chunk0, int keep_first, int window,
     int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, Index ix, int n_bh,
-    const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
+    int* __restrict__ clear, const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ stat, int64_t rows) {
     if (blockIdx.x >= n_bh) {
         bwd_row_stat<D>(out, dout, lse, stat, rows,
@@ -150,6 +150,7 @@ __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
     for (int x = lo; x < hi; ++x) {
         const int n = s_cnt[x];
         s_cnt[x] = at_ent;  // the fill's cursor
+        if (clear) clear[static_cast<int64_t>(bh) * n_chunks + x] = n == 0 || n > seg;
         for (int o = 0; o < n; o += seg)
             items[at_seg++] = make_int2(x | min(seg, n - o) << kCountShift | (n > seg) << 30,
                                         at_ent + o);
@@ -163,6 +164,28 @@ __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
     uint32_t* entries = ix.entries(bh);
     each_entry(gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
                [&](int chunk, uint32_t e) { entries[atomicAdd(&s_cnt[chunk], 1)] = e; });
+}
+
+// For a call that writes dk and dv: zeros in the rows of the chunks that the
+// lists mark (cut ones, which add, and those nobody attends) and in the rows
+// past the lists' chunks.  A workgroup looks at four chunks of a (batch, KV
+// head): most have nothing to clear.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_clear_kernel(const int* __restrict__ clear, int n_chunks,
+                                                        int64_t res_tokens, FastDiv per_bh,
+                                                        float4* __restrict__ dk,
+                                                        float4* __restrict__ dv) {
+    constexpr int VPR = D / 4;  // vectors per row
+    const int bh = per_bh.div(blockIdx.x), c0 = (blockIdx.x - bh * per_bh.d) * 4;
+    for (int chunk = c0; chunk < c0 + 4; ++chunk) {
+        const int64_t row0 = static_cast<int64_t>(chunk) * KT;
+        if (row0 >= res_tokens) return;
+        if (chunk < n_chunks && !clear[static_cast<int64_t>(bh) * n_chunks + chunk]) continue;
+        const int n = static_cast<int>(min(res_tokens - row0, static_cast<int64_t>(KT))) * VPR;
+        const int64_t at = (static_cast<int64_t>(bh) * res_tokens + row0) * VPR;
+        for (int x = threadIdx.x; x < n; x += 256)
+            dk[at + x] = dv[at + x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 }
 
 // QR query rows per step, NS steps in the LDS ring.
@@ -205,7 +228,8 @@ void bwd_chunk_kernel(
     const bf16_t* __restrict__ k_res, const bf16_t* __restrict__ v_res, int64_t res_tokens,
     const float* __restrict__ stat, const bf16_t* __restrict__ dout,
     float* __restrict__ dk, float* __restrict__ dv, FastDiv r_div,
-    FastDiv kv_div, FastDiv item_div, int group_shift, Index ix, int n_blocks, int by_xcd) {
+    FastDiv kv_div, FastDiv item_div, int group_shift, Index ix, int n_blocks, int by_xcd,
+    int write) {
     using Lay = ChunkLayout<D, QR, NS>;
     constexpr int kRow = Lay::kRow;
     constexpr int NKS = D / 32;            // 32-wide k-steps over d
@@ -378,8 +402,9 @@ void bwd_chunk_kernel(
         }
     }
 
-    // The chunk's only segment adds in place (nobody else touches its rows in
-    // this launch); the segments of a cut list add atomically.
+    // The chunk's only segment adds in place, or writes (nobody else touches
+    // its rows in this launch); the segments of a cut list add atomically (to
+    // rows that bwd_clear_kernel zeroed, when the call writes).
     const float ksc = 1.0f / sqrtf(static_cast<float>(D));
     const int64_t at0 = (static_cast<int64_t>(bh) * res_tokens + static_cast<int64_t>(chunk) * KT +
                          wave * 16 + g4 * 4) * D + l16;
@@ -390,6 +415,14 @@ void bwd_chunk_kernel(
             for (int x = 0; x < 4; ++x) {
                 unsafeAtomicAdd(dk + at0 + x * D + nb * 16, ak[nb][x] * ksc);
                 unsafeAtomicAdd(dv + at0 + x * D + nb * 16, av[nb][x]);
+            }
+    } else if (write) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                __builtin_nontemporal_store(ak[nb][x] * ksc, dk + at0 + x * D + nb * 16);
+                __builtin_nontemporal_store(av[nb][x], dv + at0 + x * D + nb * 16);
             }
     } else {
         float ok[NB][4], ov[NB][4];
@@ -438,7 +471,7 @@ IndexShape index_shape(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
     const int64_t stride = (2 * cap + entries + 3) / 4 * 4;
     const int64_t rows = static_cast<int64_t>(r) * n_q_chunks * KT;  // per (batch, KV head)
     // the row statistics and the tables live in dq
-    s.fits = n_chunks <= kBwdIndexChunks && stride + 2 * rows <= rows * p.head_dim &&
+    s.fits = n_chunks <= kBwdIndexChunks && stride + n_chunks + 2 * rows <= rows * p.head_dim &&
              cap * p.batch * p.n_kv_heads <= (int64_t(1) << 24) && entries < (int64_t(1) << 30);
     if (!s.fits) return s;
     s.per = static_cast<int>(per);
@@ -454,7 +487,7 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
                            int q_chunk0, int n_q_chunks, const void* k_res, const void* v_res,
                            int64_t res_tokens, const int32_t* group_idx, const void* out,
                            const float* lse, const void* dout, float* dq, float* dk, float* dv,
-                           hipStream_t stream) {
+                           bool write, hipStream_t stream) {
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
@@ -472,14 +505,25 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
     const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
     const Index ix{reinterpret_cast<int*>(dq + 2 * rows), sh.stride, sh.cap_items};
+    int* clear = write ? ix.base + static_cast<int64_t>(n_bh) * sh.stride : nullptr;
     const unsigned stat_blocks = static_cast<unsigned>((rows * 8 + kIndexThreads - 1) / kIndexThreads);
     hipLaunchKernelGGL((bwd_index_kernel<D>), dim3(n_bh + stat_blocks), dim3(kIndexThreads),
                        sh.n_chunks * 4, stream, group_idx, n_q_chunks, q_chunk0, p.keep_first,
                        recent_window(p), p.topk_groups, 6 - group_shift, FastDiv(sh.per),
-                       sh.n_chunks, sh.seg, ix, n_bh, static_cast<const bf16_t*>(out),
+                       sh.n_chunks, sh.seg, ix, n_bh, clear, static_cast<const bf16_t*>(out),
                        static_cast<const bf16_t*>(dout), lse, dq, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (write) {
+        const int64_t per_bh = (res_tokens + 4 * KT - 1) / (4 * KT);
+        if (per_bh * n_bh > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((bwd_clear_kernel<D>), dim3(static_cast<unsigned>(per_bh * n_bh)),
+                           dim3(256), 0, stream, clear, sh.n_chunks, res_tokens,
+                           FastDiv(static_cast<uint32_t>(per_bh)), reinterpret_cast<float4*>(dk),
+                           reinterpret_cast<float4*>(dv));
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     const int n_blocks = n_bh * sh.cap_items;
     const int by_xcd = n_bh >= 2 * kXcds;
     const int grid = by_xcd ? (n_blocks + kXcds - 1) / kXcds * kXcds : n_blocks;
@@ -488,7 +532,7 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
                        static_cast<const bf16_t*>(k_res), static_cast<const bf16_t*>(v_res),
                        res_tokens, dq, static_cast<const bf16_t*>(dout), dk, dv, FastDiv(r),
                        FastDiv(p.n_kv_heads), FastDiv(sh.cap_items), group_shift, ix, n_blocks,
-                       by_xcd);
+                       by_xcd, write);
     return hipGetLastError();
 }
 
@@ -507,14 +551,14 @@ size_t bwd_chunks_lds_bytes(const hga_plan& plan) {
 hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* group_idx, const void* out, const float* lse,
-                             const void* dout, float* dq, float* dk, float* dv,
+                             const void* dout, float* dq, float* dk, float* dv, bool write,
                              hipStream_t stream) {
     const IndexShape sh = index_shape(plan, q_chunk0, n_q_chunks);
     if (!sh.fits) return hipErrorInvalidConfiguration;
     // d64: 64 query rows a step, four workgroups per CU; d128: 32, so that three fit
     return (plan.p.head_dim == 64 ? launch_chunks_t<64, 64, 2> : launch_chunks_t<128, 32, 2>)(
         plan, sh, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx, out, lse,
-        dout, dq, dk, dv, stream);
+        dout, dq, dk, dv, write, stream);
 }
 
 }  // namespace hga

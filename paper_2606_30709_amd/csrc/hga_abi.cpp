@@ -713,11 +713,13 @@ hga_status hga_gather_attend_split(const hga_plan* plan, const void* q_rot, int3
                     "hga_gather_attend_split launch");
 }
 
-hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
-                               int32_t n_q_chunks, const void* k_res, const void* v_res,
-                               int64_t res_tokens, const int32_t* group_idx, const void* out,
-                               const float* lse, const void* dout, float* dq, float* dk,
-                               float* dv, void* stream) {
+namespace {
+
+hga_status attend_backward(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
+                           int32_t n_q_chunks, const void* k_res, const void* v_res,
+                           int64_t res_tokens, const int32_t* group_idx, const void* out,
+                           const float* lse, const void* dout, float* dq, float* dk, float* dv,
+                           bool write, void* stream) {
     HGA_TRY(check_plan(plan));
     if (q_chunk0 < 0 || n_q_chunks < 0 || res_tokens < 0)
         return fail(HGA_EINVAL, "q_chunk0, n_q_chunks and res_tokens must be >= 0");
@@ -736,8 +738,28 @@ hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t 
     clear_stale_error();
     return launched(hga::launch_attend_backward(*plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,
                                                 res_tokens, group_idx, out, lse, dout, dq, dk, dv,
-                                                static_cast<hipStream_t>(stream)),
+                                                write, static_cast<hipStream_t>(stream)),
                     "hga_attend_backward launch");
+}
+
+}  // namespace
+
+hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
+                               int32_t n_q_chunks, const void* k_res, const void* v_res,
+                               int64_t res_tokens, const int32_t* group_idx, const void* out,
+                               const float* lse, const void* dout, float* dq, float* dk,
+                               float* dv, void* stream) {
+    return attend_backward(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx,
+                           out, lse, dout, dq, dk, dv, false, stream);
+}
+
+hga_status hga_attend_backward_write(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
+                                     int32_t n_q_chunks, const void* k_res, const void* v_res,
+                                     int64_t res_tokens, const int32_t* group_idx,
+                                     const void* out, const float* lse, const void* dout,
+                                     float* dq, float* dk, float* dv, void* stream) {
+    return attend_backward(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx,
+                           out, lse, dout, dq, dk, dv, true, stream);
 }
 
 hga_status hga_gather_attend(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,

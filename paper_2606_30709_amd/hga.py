@@ -21,7 +21,7 @@ __all__ = [
     "hga_attend_timed", "hga_attend_split", "hga_attend_split_workspace",
     "hga_attend_split_static", "hga_static_scratch_bytes", "hga_gather_attend",
     "hga_gather_attend_split", "hga_gather_kv_cached", "hga_attend_backward",
-    "hga_block_step", "hga_prefill_blocks", "hga_status_string", "hga_last_error",
+    "hga_attend_backward_write", "hga_block_step", "hga_prefill_blocks", "hga_status_string", "hga_last_error",
     "hga_version", "hga_visible_chunks", "EXPORTED_SYMBOLS",
 ]
 
@@ -34,8 +34,8 @@ EXPORTED_SYMBOLS = (
     "hga_route_qbar", "hga_gather_kv", "hga_attend", "hga_attend_timed", "hga_attend_split",
     "hga_attend_split_workspace", "hga_attend_split_static", "hga_static_scratch_bytes",
     "hga_gather_attend", "hga_gather_attend_split",
-    "hga_gather_kv_cached", "hga_attend_backward", "hga_block_step", "hga_prefill_blocks",
-    "hga_status_string",
+    "hga_gather_kv_cached", "hga_attend_backward", "hga_attend_backward_write",
+    "hga_block_step", "hga_prefill_blocks", "hga_status_string",
     "hga_last_error", "hga_version", "hga_visible_chunks",
 )
 
@@ -98,6 +98,8 @@ def library() -> ctypes.CDLL:
             "hga_gather_attend": [vp, vp, i32, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp, vp],
             "hga_attend_backward": [vp, vp, i32, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp,
                                     vp],
+            "hga_attend_backward_write": [vp, vp, i32, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp,
+                                          vp, vp],
             "hga_gather_attend_split": [vp, vp, i32, i32, vp, vp, i64, vp, vp, vp, i64, i32, vp,
                                         vp, vp, vp, vp, vp, i64, vp],
             "hga_block_step": [vp, vp, i32, vp, vp, i64, vp, vp, i32, vp, vp, vp, vp, vp, vp,
@@ -403,6 +405,16 @@ def hga_attend_backward(plan: Plan, q_rot, q_chunk0: int, k_res, v_res, group_id
     fp32 written; dk, dv [B, Hkv, res_tokens, d] fp32 added into."""
     nq = q_rot.shape[2] // plan.params.chunk
     _check(library().hga_attend_backward(
+        plan.handle, _ptr(q_rot), q_chunk0, nq, _ptr(k_res), _ptr(v_res), k_res.shape[2],
+        _ptr(group_idx), _ptr(out), _ptr(lse), _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv),
+        _stream(stream)))
+
+
+def hga_attend_backward_write(plan: Plan, q_rot, q_chunk0: int, k_res, v_res, group_idx, out, lse,
+                              dout, dq, dk, dv, stream=None):
+    """hga_attend_backward with dk, dv written over every row instead of added into."""
+    nq = q_rot.shape[2] // plan.params.chunk
+    _check(library().hga_attend_backward_write(
         plan.handle, _ptr(q_rot), q_chunk0, nq, _ptr(k_res), _ptr(v_res), k_res.shape[2],
         _ptr(group_idx), _ptr(out), _ptr(lse), _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv),
         _stream(stream)))

@@ -42,6 +42,20 @@ def _check(w, q0, gi, seed):
     for i in range(n):  # absent: outside the causal past
         row = valid[:, :, i]
         row[(row < 0) | (row >= (q0 + i) * (C // G))] = -1
+    # the writing form: the same sums over zeros, whatever the buffers held; the
+    # rows of a resident buffer past the last chunk are written too
+    pad = [torch.cat([t, torch.full_like(t[:, :, :70], float("nan"))], 2) for t in dev[1:3]]
+    wq = torch.full_like(dq, float("nan"))
+    wk = torch.full(pad[0].shape, float("nan"), device="cuda")
+    wv = wk.clone()
+    hga.hga_attend_backward_write(plan, dev[0], q0, pad[0], pad[1], ids, out, lse, dev[3], wq, wk, wv)
+    torch.cuda.synchronize()
+    assert torch.equal(wq, dq)
+    for got, added in ((wk, dk - base), (wv, dv + base)):
+        tail = got[:, :, w.seq_len:]
+        assert bool((tail == 0).all())
+        top = added.abs().max()
+        assert (got[:, :, :w.seq_len] - added).abs().max() <= 1e-5 * (top + base.abs().max())
     x = [f64(t.view(torch.int16).numpy().view(np.uint16), "bf16") for t in (q, k, v, dout)]
     ref = O.attend_backward(x[0], x[1], x[2], x[3], valid, list(range(q0, w.n_chunks)), C, G,
                             w.keep_first, w.keep_last, w.force_prev)
