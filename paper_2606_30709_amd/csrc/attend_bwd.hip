@@ -197,7 +197,7 @@ void attend_bwd_dq_kernel(
 #pragma unroll
     for (int u = 0; u < KI; ++u) {
         const int slot = (u * NW + wave) * 64 + lane, row = slot / (D / 8);
-        koff[u] = row * kRow + ((slot % (D / 8)) ^ swz<D>(row)) * 16;
+        koff[u] = row * kRow + ((slot % (D / 8)) ^ swz_rows<D>(row)) * 16;
     }
     auto issue = [&](int tile, int stage) {
         uint32_t src[KI];
@@ -237,14 +237,14 @@ void attend_bwd_dq_kernel(
     // rows further on are immediates
     int aoff[NKS], toff[2][NDT];
 #pragma unroll
-    for (int kk = 0; kk < NKS; ++kk) aoff[kk] = col * kRow + (((2 * kk + half) ^ swz<D>(col)) * 16);
+    for (int kk = 0; kk < NKS; ++kk) aoff[kk] = col * kRow + (((2 * kk + half) ^ swz_rows<D>(col)) * 16);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             const int row = x * 8 + half * 4 + ((lane & 15) >> 2);
             const int ch = dt * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
-            toff[x][dt] = row * kRow + ((ch ^ swz<D>(row)) * 16) + (lane & 1) * 8;
+            toff[x][dt] = row * kRow + ((ch ^ swz_rows<D>(row)) * 16) + (lane & 1) * 8;
         }
 
     for (int tile = 0; tile < n_tiles; ++tile) {

@@ -25,19 +25,6 @@ hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chun
                              const void* dout, float* dq, float* dk, float* dv, bool write,
                              hipStream_t stream);
 
-// 16-byte chunk j of staged row r is stored at j ^ swz(r).  The 16-byte
-// fragment reads of 16 consecutive rows then fall in distinct banks, and so
-// do the transpose reads (32 bytes of rows 0..7, or of rows 0..3 and 8..11, or
-// 64 bytes of rows 0..3 of a 16-row block in one cycle).
-template <int D>
-__device__ __forceinline__ int swz(int r) {
-    if constexpr (D == 64)  // two rows span the banks: r >> 1 counts
-        return (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) | ((r >> 3) & 1);
-    else
-        return ((r & 1) << 3) | (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) |
-               ((r >> 3) & 1);
-}
-
 // Workgroup barrier that orders LDS only: waits for this wave's LDS
 // operations, not for its copies or atomics.
 __device__ __forceinline__ void lds_barrier() {

@@ -273,7 +273,7 @@ void bwd_chunk_kernel(
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
         const int row = (u * 4 + wave) * RPC + lane / CPR;
-        koff[u] = row * kRow + (((lane % CPR) ^ swz<D>(row)) * 16);
+        koff[u] = row * kRow + (((lane % CPR) ^ swz_rows<D>(row)) * 16);
     }
     auto issue = [&](int s, int stage) {
         const int x = s / SPU, ent = r_div.div(x), hh = x - ent * r;
@@ -321,11 +321,11 @@ void bwd_chunk_kernel(
     // 16-row blocks are immediates
     int aoff[NKS], toff[NB];
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) aoff[ks] = l16 * kRow + (((ks * 4 + g4) ^ swz<D>(l16)) * 16);
+    for (int ks = 0; ks < NKS; ++ks) aoff[ks] = l16 * kRow + (((ks * 4 + g4) ^ swz_rows<D>(l16)) * 16);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int row = g4 * 4 + (l16 >> 2);  // four queries of one dimension per transpose read
-        toff[nb] = row * kRow + (((nb * 2 + ((l16 & 3) >> 1)) ^ swz<D>(row)) * 16) + (l16 & 1) * 8;
+        toff[nb] = row * kRow + (((nb * 2 + ((l16 & 3) >> 1)) ^ swz_rows<D>(row)) * 16) + (l16 & 1) * 8;
     }
     const bool split_groups = group_shift == 3;  // a wavefront's keys are two groups
 

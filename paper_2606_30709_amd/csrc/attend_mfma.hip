@@ -1036,6 +1036,11 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
         return launch_attend(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                              res_slot, k_routed, v_routed, group_idx, out, lse, nullptr, nullptr,
                              stream);
+    if (attend_few_applies(plan, n_q_chunks))
+        return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                                 res_slot, const_cast<void*>(k_routed),
+                                 const_cast<void*>(v_routed), group_idx, out, lse, stream, nullptr,
+                                 nullptr, 0);
     return launch_split_any<false>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                    res_slot, k_routed, v_routed, group_idx, out, lse,
                                    static_cast<float*>(workspace), n_split, stream);
@@ -1047,7 +1052,8 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                       const void* k_src, const void* v_src, int64_t src_tokens,
                                       const int32_t* group_idx, void* k_routed, void* v_routed,
                                       void* out, float* lse, void* workspace,
-                                      int64_t workspace_bytes, hipStream_t stream) {
+                                      int64_t workspace_bytes, bool src_on_host,
+                                      hipStream_t stream) {
     const hga_params& p = plan.p;
     if (p.dtype == HGA_F32) {
         // the gather kernel, then the attention reading its output; without
@@ -1066,6 +1072,32 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
         return launch_mfma_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                      res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,
                                      nullptr, stream, k_src, v_src, src_tokens);
+    if (attend_few_applies(plan, n_q_chunks)) {
+        // Every query tile's workgroup copies the routed rows.  Over the host
+        // link they pass once instead: gathered to the routed buffers, or to
+        // the workspace when there are none and it is large enough.
+        if (src_on_host) {
+            const int64_t bytes = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks *
+                                  p.topk_groups * p.group * p.head_dim * 2;
+            void* kr = k_routed;
+            void* vr = v_routed;
+            if (!kr && 2 * bytes <= workspace_bytes) {
+                kr = workspace;
+                vr = static_cast<unsigned char*>(workspace) + bytes;
+            }
+            if (kr) {
+                const hipError_t e = launch_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_src,
+                                                      v_src, src_tokens, kr, vr, stream);
+                if (e != hipSuccess) return e;
+                return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,
+                                         res_tokens, res_slot, kr, vr, group_idx, out, lse,
+                                         stream, nullptr, nullptr, 0);
+            }
+        }
+        return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                                 res_slot, k_routed, v_routed, group_idx, out, lse, stream, k_src,
+                                 v_src, src_tokens);
+    }
     return launch_split_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   res_slot, k_routed, v_routed, group_idx, out, lse,
                                   static_cast<float*>(workspace), n_split, stream, k_src, v_src,

@@ -709,7 +709,8 @@ hga_status hga_gather_attend_split(const hga_plan* plan, const void* q_rot, int3
     return launched(hga::launch_gather_attend_split(
                         *plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, res_slot,
                         ks, vs, src_tokens, group_idx, k_routed, v_routed, out, lse, workspace,
-                        workspace ? workspace_bytes : 0, static_cast<hipStream_t>(stream)),
+                        workspace ? workspace_bytes : 0, src_on_host != 0,
+                        static_cast<hipStream_t>(stream)),
                     "hga_gather_attend_split launch");
 }
 
@@ -825,7 +826,7 @@ hipError_t launch_block_step(const hga_plan& plan, const void* q_block, int32_t 
         e = hga::launch_gather_attend_split(plan, q_block, c, 1, k_res, v_res, res_tokens, nullptr,
                                             k_res, v_res, res_tokens, group_idx, k_routed,
                                             v_routed, out, lse, workspace, workspace_bytes,
-                                            stream);
+                                            false, stream);
     else
         e = hga::launch_gather_attend(plan, q_block, c, 1, k_res, v_res, res_tokens, group_idx,
                                       k_routed, v_routed, out, lse, nullptr, nullptr, stream);

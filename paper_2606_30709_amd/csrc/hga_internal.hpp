@@ -143,6 +143,16 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
                                float* lse, void* workspace, int64_t workspace_bytes,
                                hipStream_t stream);
 
+// The attention of a few units in one launch: every key of a query tile in one
+// workgroup.  Routed rows from k_routed / v_routed, or (k_src given) gathered
+// from k_src / v_src and written to k_routed / v_routed when those are given.
+bool attend_few_applies(const hga_plan& plan, int n_q_chunks);
+hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
+                             const void* k_res, const void* v_res, int64_t res_tokens,
+                             const int32_t* res_slot, void* k_routed, void* v_routed,
+                             const int32_t* group_idx, void* out, float* lse, hipStream_t stream,
+                             const void* k_src, const void* v_src, int64_t src_tokens);
+
 // Backward of the attention (bf16): dq written, dk and dv (fp32, resident
 // layout) accumulated into or (`write`) written over every resident row.
 size_t attend_backward_lds_bytes(const hga_plan& plan);
@@ -163,7 +173,8 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                       const void* k_src, const void* v_src, int64_t src_tokens,
                                       const int32_t* group_idx, void* k_routed, void* v_routed,
                                       void* out, float* lse, void* workspace,
-                                      int64_t workspace_bytes, hipStream_t stream);
+                                      int64_t workspace_bytes, bool src_on_host,
+                                      hipStream_t stream);
 
 // The gather of the routed rows fused into the attention (prefill layout:
 // resident K/V indexed by token, no slot map); writes k_routed / v_routed as

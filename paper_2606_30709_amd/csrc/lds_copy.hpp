@@ -55,4 +55,17 @@ __device__ __forceinline__ void lds_reads_done() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
+// Row-major staging of bf16 rows of D dimensions: 16-byte chunk j of row r is stored at j ^ swz_rows(r).  The 16-byte
+// fragment reads of 16 consecutive rows then fall in distinct banks, and so
+// do the transpose reads (32 bytes of rows 0..7, or of rows 0..3 and 8..11, or
+// 64 bytes of rows 0..3 of a 16-row block in one cycle).
+template <int D>
+__device__ __forceinline__ int swz_rows(int r) {
+    if constexpr (D == 64)  // two rows span the banks: r >> 1 counts
+        return (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) | ((r >> 3) & 1);
+    else
+        return ((r & 1) << 3) | (((r >> 1) & 1) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) |
+               ((r >> 3) & 1);
+}
+
 }  // namespace hga
