@@ -529,8 +529,10 @@ hga_status hga_block_step(const hga_plan* plan, const void* q_block, int32_t c,
                           void* out, float* lse, void* workspace, int64_t workspace_bytes,
                           void* stream);
 
-/* A block-sequential prefill of blocks 0 .. n_blocks-1: hga_block_step for
- * c = 0, 1, ... in order, all enqueued on `stream`.  Block c reads and
+/* A block-sequential prefill of blocks 0 .. n_blocks-1: what hga_block_step
+ * for c = 0, 1, ... in order writes.  The whole prompt is given, and no
+ * block's routing or attention reads what another block's attention wrote, so
+ * the blocks are computed together, one launch per step.  Block c reads and
  * writes the c-th slice of each block-major buffer:
  *   q_blocks, out   [n_blocks][batch, n_q_heads, chunk, head_dim]
  *   lse             [n_blocks][batch, n_q_heads, chunk] fp32 or NULL
@@ -543,8 +545,7 @@ hga_status hga_block_step(const hga_plan* plan, const void* q_block, int32_t c,
  * blocks close.  Every block's outputs equal what the bulk prefill
  * (hga_build_summaries, then hga_route and hga_gather_attend over all chunks)
  * writes for the same query chunk.  Arguments are checked before the first
- * launch; an error returned by a later launch leaves the earlier blocks done.
- * workspace / workspace_bytes as for hga_block_step. */
+ * launch.  workspace / workspace_bytes as for hga_block_step. */
 hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_t n_blocks,
                               const void* k_res, const void* v_res, int64_t res_tokens,
                               float* chunk_sum, float* group_sum, int32_t table_chunks,

@@ -84,7 +84,7 @@ void attend_f32_kernel(
     const int32_t* __restrict__ group_idx, float* __restrict__ out, float* __restrict__ lse, int r,
     FastDiv kv_div, FastDiv chunk_div, FastDiv tile_div, int group_shift, int keep_first,
     int window, int topk_groups, const float* __restrict__ k_src, const float* __restrict__ v_src,
-    int64_t src_tokens, int n_items) {
+    int64_t src_tokens, int n_items, ChunkMap q_map, ChunkMap unit_map) {
     using Lay = F32Layout<D>;
     constexpr int kRow = Lay::kRow;
     constexpr int CPR = D / 4;               // 16-byte chunks per row
@@ -98,10 +98,11 @@ void attend_f32_kernel(
     const int per_xcd = (n_items + kXcds - 1) / kXcds;
     const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     if (item >= n_items) return;
-    const int unit = tile_div.div(item);
-    const int qtile = item - unit * tile_div.d;
-    const int bh = chunk_div.div(unit);
-    const int i = unit - bh * n_q_chunks;
+    const int unit_id = tile_div.div(item);
+    const int qtile = item - unit_id * tile_div.d;
+    const int bh = chunk_div.div(unit_id);
+    const int i = unit_id - bh * n_q_chunks;
+    const int64_t unit = unit_map.at(bh, i);
     const int b = kv_div.div(bh), j = bh - b * kv_div.d;
     const int c = q_chunk0 + i;
 
@@ -114,9 +115,7 @@ void attend_f32_kernel(
 
     const int n_q_heads = r * kv_div.d;
     const int hh = qtile >> 1, tq = qtile & 1;  // head of the group, half of the chunk
-    const int64_t row0 = (static_cast<int64_t>(b) * n_q_heads + j * r + hh) *
-                             (static_cast<int64_t>(n_q_chunks) * KT) +
-                         static_cast<int64_t>(i) * KT + tq * ST;  // the first query row
+    const int64_t row0 = q_map.at(b * n_q_heads + j * r + hh, i) * KT + tq * ST;  // the first query row
     const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(D));  // log2(e)/sqrt(d)
     const int64_t res_chunks = res_tokens / KT;
     const int routed_rows = topk_groups << group_shift;
@@ -130,7 +129,7 @@ void attend_f32_kernel(
     // of its groups
     const bool from_src = k_routed == nullptr;
     const int64_t rt_off = from_src ? static_cast<int64_t>(bh) * src_tokens * D
-                                    : static_cast<int64_t>(unit) * routed_rows * D;
+                                    : unit * routed_rows * D;
     const uint32_t rt_bytes = from_src ? static_cast<uint32_t>(src_tokens * kRow)
                                        : static_cast<uint32_t>(routed_rows * kRow);
     const u32x4 rk_rt = rsrc_words((from_src ? k_src : k_routed) + rt_off, rt_bytes);
@@ -138,7 +137,7 @@ void attend_f32_kernel(
 
     // the unit's group ids, one copy per wavefront (no barrier needed)
     {
-        const u32x4 rg = rsrc_words(group_idx + static_cast<int64_t>(unit) * topk_groups,
+        const u32x4 rg = rsrc_words(group_idx + unit * topk_groups,
                                     topk_groups * 4);
         for (int u = 0; u * 64 < topk_groups; ++u)
             copy4_to_lds(rg, (u * 64 + lane) * 4, lds0 + Lay::kGid + u * 256);
@@ -351,7 +350,7 @@ hipError_t launch_f32_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
                         const int32_t* res_slot, const void* k_routed, const void* v_routed,
                         const int32_t* group_idx, void* out, float* lse, hipEvent_t ev_start,
                         hipEvent_t ev_stop, hipStream_t stream, const void* k_src,
-                        const void* v_src, int64_t src_tokens) {
+                        const void* v_src, int64_t src_tokens, bool block_major) {
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per kernel and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
@@ -374,7 +373,9 @@ hipError_t launch_f32_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
                           FastDiv(n_q_chunks), FastDiv(2 * r), group_shift, p.keep_first,
                           recent_window(p), p.topk_groups, static_cast<const float*>(k_src),
                           static_cast<const float*>(v_src), src_tokens,
-                          static_cast<int>(items));
+                          static_cast<int>(items),
+                          chunk_map(p.batch * p.n_q_heads, n_q_chunks, block_major),
+                          chunk_map(p.batch * p.n_kv_heads, n_q_chunks, block_major));
     return hipGetLastError();
 }
 
@@ -385,10 +386,10 @@ hipError_t launch_attend_f32(const hga_plan& plan, const void* q_rot, int q_chun
                              const int32_t* res_slot, const void* k_routed, const void* v_routed,
                              const int32_t* group_idx, void* out, float* lse, hipEvent_t ev_start,
                              hipEvent_t ev_stop, hipStream_t stream, const void* k_src,
-                             const void* v_src, int64_t src_tokens) {
+                             const void* v_src, int64_t src_tokens, bool block_major) {
     return (plan.p.head_dim == 64 ? launch_f32_t<64> : launch_f32_t<128>)(
         plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, res_slot, k_routed, v_routed,
-        group_idx, out, lse, ev_start, ev_stop, stream, k_src, v_src, src_tokens);
+        group_idx, out, lse, ev_start, ev_stop, stream, k_src, v_src, src_tokens, block_major);
 }
 
 }  // namespace hga

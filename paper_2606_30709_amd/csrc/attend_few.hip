@@ -71,7 +71,8 @@ void attend_few_kernel(
     bf16_t* __restrict__ v_routed, const int32_t* __restrict__ group_idx,
     bf16_t* __restrict__ out, float* __restrict__ lse, int r, FastDiv kv_div, FastDiv chunk_div,
     FastDiv tile_div, int group_shift, int keep_first, int window, int topk_groups,
-    const bf16_t* __restrict__ k_src, const bf16_t* __restrict__ v_src, int64_t src_tokens) {
+    const bf16_t* __restrict__ k_src, const bf16_t* __restrict__ v_src, int64_t src_tokens,
+    ChunkMap q_map, ChunkMap unit_map) {
     using Lay = FewLayout<D>;
     constexpr int kRow = Lay::kRow;
     constexpr int CPR = D / 8;             // 16-byte chunks per row
@@ -80,10 +81,11 @@ void attend_few_kernel(
     constexpr int NKS = D / 16, NDT = D / 32;
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int unit = tile_div.div(blockIdx.x);
-    const int qtile = blockIdx.x - unit * tile_div.d;
-    const int bh = chunk_div.div(unit);
-    const int i = unit - bh * n_q_chunks;
+    const int item = tile_div.div(blockIdx.x);
+    const int qtile = blockIdx.x - item * tile_div.d;
+    const int bh = chunk_div.div(item);
+    const int i = item - bh * n_q_chunks;
+    const int64_t unit = unit_map.at(bh, i);
     const int b = kv_div.div(bh), j = bh - b * kv_div.d;
     const int c = q_chunk0 + i;
 
@@ -95,9 +97,8 @@ void attend_few_kernel(
     const int* s_gid = reinterpret_cast<const int*>(mine + Lay::kGid);
 
     const int hh = qtile >> 1, tq = qtile & 1;  // head of the group, half of the chunk
-    const int64_t row0 = (static_cast<int64_t>(b) * (r * kv_div.d) + j * r + hh) *
-                             (static_cast<int64_t>(n_q_chunks) * KT) +
-                         static_cast<int64_t>(i) * KT + tq * ST;  // the tile's first query row
+    // the tile's first query row
+    const int64_t row0 = q_map.at(b * (r * kv_div.d) + j * r + hh, i) * KT + tq * ST;
     const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(D));  // log2(e)/sqrt(d)
     const int64_t res_chunks = res_tokens / KT;
     const int routed_rows = topk_groups << group_shift;
@@ -108,14 +109,14 @@ void attend_few_kernel(
     const u32x4 rv_res = rsrc_words(v_res + static_cast<int64_t>(bh) * res_tokens * D,
                                     static_cast<uint32_t>(res_tokens * kRow));
     const int64_t rt_off = kGather ? static_cast<int64_t>(bh) * src_tokens * D
-                                   : static_cast<int64_t>(unit) * routed_rows * D;
+                                   : unit * routed_rows * D;
     const uint32_t rt_bytes = static_cast<uint32_t>((kGather ? src_tokens : routed_rows) * kRow);
     const u32x4 rk_rt = rsrc_words((kGather ? k_src : k_routed) + rt_off, rt_bytes);
     const u32x4 rv_rt = rsrc_words((kGather ? v_src : v_routed) + rt_off, rt_bytes);
 
     // the unit's group ids, one copy per wavefront
     {
-        const u32x4 rg = rsrc_words(group_idx + static_cast<int64_t>(unit) * topk_groups,
+        const u32x4 rg = rsrc_words(group_idx + unit * topk_groups,
                                     topk_groups * 4);
         for (int u = 0; u * 64 < topk_groups; ++u)
             copy4_to_lds(rg, (u * 64 + lane) * 4, lds0 + Lay::kGid + u * 256);
@@ -191,7 +192,7 @@ void attend_few_kernel(
     // this lane's slots of a staged routed sub-tile to the routed buffer
     auto write_rows = [&](int rs, const unsigned char* staged, bf16_t* dst) {
         unsigned char* at = reinterpret_cast<unsigned char*>(dst) +
-                            (static_cast<int64_t>(unit) * routed_rows + rs * ST) * kRow;
+                            (unit * routed_rows + rs * ST) * kRow;
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
             const int row = u * RPC + crow;
@@ -343,7 +344,7 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
                         const void* k_res, const void* v_res, int64_t res_tokens,
                         const int32_t* res_slot, void* k_routed, void* v_routed,
                         const int32_t* group_idx, void* out, float* lse, hipStream_t stream,
-                        const void* k_src, const void* v_src, int64_t src_tokens) {
+                        const void* k_src, const void* v_src, int64_t src_tokens, bool block_major) {
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
@@ -362,7 +363,9 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
                        static_cast<bf16_t*>(out), lse, r, FastDiv(p.n_kv_heads),
                        FastDiv(n_q_chunks), FastDiv(2 * r), group_shift, p.keep_first,
                        recent_window(p), p.topk_groups, static_cast<const bf16_t*>(k_src),
-                       static_cast<const bf16_t*>(v_src), src_tokens);
+                       static_cast<const bf16_t*>(v_src), src_tokens,
+                       chunk_map(p.batch * p.n_q_heads, n_q_chunks, block_major),
+                       chunk_map(p.batch * p.n_kv_heads, n_q_chunks, block_major));
     return hipGetLastError();
 }
 
@@ -381,12 +384,13 @@ hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chun
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* res_slot, void* k_routed, void* v_routed,
                              const int32_t* group_idx, void* out, float* lse, hipStream_t stream,
-                             const void* k_src, const void* v_src, int64_t src_tokens) {
+                             const void* k_src, const void* v_src, int64_t src_tokens,
+                             bool block_major) {
     const bool d64 = plan.p.head_dim == 64, gather = k_src != nullptr;
     return (d64 ? (gather ? launch_few_t<64, true> : launch_few_t<64, false>)
                 : (gather ? launch_few_t<128, true> : launch_few_t<128, false>))(
         plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, res_slot, k_routed, v_routed,
-        group_idx, out, lse, stream, k_src, v_src, src_tokens);
+        group_idx, out, lse, stream, k_src, v_src, src_tokens, block_major);
 }
 
 }  // namespace hga

@@ -455,7 +455,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
     bf16_t* __restrict__ out, float* __restrict__ lse, int r, FastDiv kv_div, int group_shift,
     int keep_first, int window, int topk_groups, FastDiv wg_div, FastDiv chunk_div,
     int n_blocks, float* __restrict__ partial_ws, FastDiv split_div,
-    const bf16_t* __restrict__ k_src, const bf16_t* __restrict__ v_src, int64_t src_tokens) {
+    const bf16_t* __restrict__ k_src, const bf16_t* __restrict__ v_src, int64_t src_tokens,
+    ChunkMap q_map, ChunkMap unit_map) {
     static_assert(!kSplit || KS == 1, "split form: one wavefront per query tile");
     using Lay = Layout<D, NS>;
     constexpr uint32_t kRowBytes = Lay::kRowBytes, kTileBytes = Lay::kTileBytes,
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
     const int qtile = part * QT + qt_local;
     const int ksplit = wave / QT;
     const bool qactive = qtile < nqt;
-    const int64_t unit = unit_id;
+    const int64_t unit = unit_map.at(bh, i);
     const int routed_rows = topk_groups * group;
     const int64_t res_chunks = res_tokens / KT;
 
@@ -542,9 +543,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
     // this lane's query row (token t of head hh)
     const int qrow_in_unit = qtile * 32 + col;
     const int hh = qrow_in_unit / KT, t = qrow_in_unit % KT;
-    const int64_t qrow = (static_cast<int64_t>(b) * n_q_heads + j * r + (qactive ? hh : 0)) *
-                             (static_cast<int64_t>(n_q_chunks) * KT) +
-                         static_cast<int64_t>(i) * KT + t;
+    const int64_t qrow = q_map.at(b * n_q_heads + j * r + (qactive ? hh : 0), i) * KT + t;
     // Query fragments (B operand of S^T = K.Q^T), straight from global
     // memory into registers: row qrow, dimensions kk*16 + half*8 .. +8.
     // They are requested before any key tile, so they have arrived once the
@@ -850,7 +849,7 @@ hipError_t launch_mfma_t(const hga_plan& plan, hipStream_t stream, hipEvent_t ev
                          const int32_t* group_idx, bf16_t* out, float* lse, int group_shift,
                          int wg_per_unit, int n_items, float* part = nullptr, int n_split = 1,
                          const bf16_t* k_src = nullptr, const bf16_t* v_src = nullptr,
-                         int64_t src_tokens = 0) {
+                         int64_t src_tokens = 0, bool block_major = false) {
     const hga_params& p = plan.p;
     if (!k_src) {  // routed rows (kGather) from the resident K/V
         k_src = k_res;
@@ -872,7 +871,9 @@ hipError_t launch_mfma_t(const hga_plan& plan, hipStream_t stream, hipEvent_t ev
                           group_idx, out, lse, p.n_q_heads / p.n_kv_heads, FastDiv(p.n_kv_heads),
                           group_shift, p.keep_first, recent_window(p), p.topk_groups,
                           FastDiv(wg_per_unit), FastDiv(n_q_chunks), n_items, part,
-                          FastDiv(n_split), k_src, v_src, src_tokens);
+                          FastDiv(n_split), k_src, v_src, src_tokens,
+                          chunk_map(p.batch * p.n_q_heads, n_q_chunks, block_major),
+                          chunk_map(p.batch * p.n_kv_heads, n_q_chunks, block_major));
     return hipGetLastError();
 }
 
@@ -890,7 +891,8 @@ hipError_t launch_mfma_any(const hga_plan& plan, const void* q_rot, int q_chunk0
                            const int32_t* res_slot, void* k_routed, void* v_routed,
                            const int32_t* group_idx, void* out, float* lse, hipEvent_t ev_start,
                            hipEvent_t ev_stop, hipStream_t stream, const void* k_src = nullptr,
-                           const void* v_src = nullptr, int64_t src_tokens = 0) {
+                           const void* v_src = nullptr, int64_t src_tokens = 0,
+                           bool block_major = false) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
     const int nqt = 2 * r;
@@ -915,7 +917,8 @@ hipError_t launch_mfma_any(const hga_plan& plan, const void* q_rot, int q_chunk0
     const bf16_t* vs = static_cast<const bf16_t*>(v_src);
 #define HGA_ARGS                                                                                 \
     plan, stream, ev_start, ev_stop, q, q_chunk0, n_q_chunks, kr, vr, res_tokens, res_slot, kt, \
-        vt, group_idx, o, lse, group_shift, wg_per_unit, n_items, nullptr, 1, ks, vs, src_tokens
+        vt, group_idx, o, lse, group_shift, wg_per_unit, n_items, nullptr, 1, ks, vs, src_tokens,    \
+        block_major
     if (p.head_dim == 64) {
         if (one_head) return launch_mfma_t<64, 2, 2, 4, kGather>(HGA_ARGS);
         return launch_mfma_t<64, 1, 2, 4, kGather>(HGA_ARGS);
@@ -984,7 +987,8 @@ hipError_t launch_attend_f32(const hga_plan& plan, const void* q_rot, int q_chun
                               const void* v_routed, const int32_t* group_idx, void* out,
                               float* lse, hipEvent_t ev_start, hipEvent_t ev_stop,
                               hipStream_t stream, const void* k_src = nullptr,
-                              const void* v_src = nullptr, int64_t src_tokens = 0);
+                              const void* v_src = nullptr, int64_t src_tokens = 0,
+                              bool block_major = false);
 
 int64_t attend_split_bytes_per_split(const hga_plan& plan, int n_q_chunks) {
     const hga_params& p = plan.p;
@@ -1125,23 +1129,24 @@ hipError_t launch_gather_attend(const hga_plan& plan, const void* q_rot, int q_c
                                 int n_q_chunks, const void* k_res, const void* v_res,
                                 int64_t res_tokens, const int32_t* group_idx, void* k_routed,
                                 void* v_routed, void* out, float* lse, hipEvent_t ev_start,
-                                hipEvent_t ev_stop, hipStream_t stream) {
+                                hipEvent_t ev_stop, hipStream_t stream, bool block_major) {
     if (plan.p.dtype == HGA_F32) {
         // fp32: the gather kernel, then the attention kernel reading its
         // output; without routed buffers the attention kernel reads each
         // routed row from the resident K/V itself
         if (k_routed) {
             const hipError_t e = launch_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_res,
-                                                  v_res, res_tokens, k_routed, v_routed, stream);
+                                                  v_res, res_tokens, k_routed, v_routed, stream,
+                                                  block_major);
             if (e != hipSuccess) return e;
         }
         return launch_attend_f32(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   nullptr, k_routed, v_routed, group_idx, out, lse, ev_start,
-                                  ev_stop, stream, k_res, v_res, res_tokens);
+                                  ev_stop, stream, k_res, v_res, res_tokens, block_major);
     }
     return launch_mfma_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                  nullptr, k_routed, v_routed, group_idx, out, lse, ev_start,
-                                 ev_stop, stream);
+                                 ev_stop, stream, nullptr, nullptr, 0, block_major);
 }
 
 }  // namespace hga

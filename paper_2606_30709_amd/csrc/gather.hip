@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(
     const int32_t* __restrict__ group_idx, int q_chunk0, int n_q_chunks, int topk, int group,
     int gpc, const unsigned char* __restrict__ k_src, const unsigned char* __restrict__ v_src,
     int64_t src_tokens, unsigned char* __restrict__ k_out, unsigned char* __restrict__ v_out,
-    int64_t total_vec, int elem_bytes) {
+    int64_t total_vec, int elem_bytes, int block_bh) {
     constexpr int VPR = D / V;
     const int64_t row_bytes = static_cast<int64_t>(D) * elem_bytes;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
@@ -38,11 +38,12 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(
             if (idx >= total_vec) continue;
             const int64_t row = idx / VPR;
             const int cv = static_cast<int>(idx % VPR);
-            const int64_t unit = row / rows_per_unit;          // (b * n_kv + j) * n_q_chunks + i
+            // (b * n_kv + j) * n_q_chunks + i, or block-major i * block_bh + b * n_kv + j
+            const int64_t unit = row / rows_per_unit;
             const int in_unit = static_cast<int>(row % rows_per_unit);
             const int s = in_unit / group, o = in_unit % group;
-            const int i = static_cast<int>(unit % n_q_chunks);
-            const int64_t bh = unit / n_q_chunks;
+            const int i = static_cast<int>(block_bh ? unit / block_bh : unit % n_q_chunks);
+            const int64_t bh = block_bh ? unit % block_bh : unit / n_q_chunks;
             const int g = group_idx[unit * topk + s];
             const int c = q_chunk0 + i;
             const bool ok = g >= 0 && g < c * gpc &&
@@ -326,7 +327,7 @@ hipError_t launch_gather_kv_cached(const hga_plan& plan, const int32_t* group_id
 hipError_t launch_gather_kv(const hga_plan& plan, const int32_t* group_idx, int q_chunk0,
                             int n_q_chunks, const void* k_src, const void* v_src,
                             int64_t src_tokens, void* k_routed, void* v_routed,
-                            hipStream_t stream) {
+                            hipStream_t stream, bool block_major) {
     const hga_params& p = plan.p;
     const int eb = p.dtype == HGA_F32 ? 4 : 2;
     const int V = 16 / eb;
@@ -344,7 +345,8 @@ hipError_t launch_gather_kv(const hga_plan& plan, const int32_t* group_idx, int 
 #define HGA_GATHER(DD, VV)                                                                        \
     hipLaunchKernelGGL((gather_kernel<DD, VV>), dim3(static_cast<unsigned>(blocks)),             \
                        dim3(kThreads), 0, stream, group_idx, q_chunk0, n_q_chunks, p.topk_groups, \
-                       p.group, gpc, ks, vs, src_tokens, ko, vo, total_vec, eb)
+                       p.group, gpc, ks, vs, src_tokens, ko, vo, total_vec, eb,                   \
+                       block_major ? p.batch * p.n_kv_heads : 0)
     if (p.head_dim == 64) {
         if (V == 4) HGA_GATHER(64, 4); else HGA_GATHER(64, 8);
     } else {

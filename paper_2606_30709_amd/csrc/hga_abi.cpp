@@ -891,17 +891,29 @@ hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_
             atw(out, c * q_bytes), lse ? lse + c * bq : nullptr));
     }
     clear_stale_error();
-    for (int32_t c = 0; c < n_blocks; ++c) {
-        const hipError_t e = launch_block_step(
-            *plan, at(q_blocks, c * q_bytes), c, k_res, v_res, res_tokens, chunk_sum, group_sum,
-            table_chunks, qbar + c * qbar_elems, chunk_idx + c * ci_elems,
-            group_idx + c * gi_elems, atw(k_routed, c * rt_bytes), atw(v_routed, c * rt_bytes),
-            atw(out, c * q_bytes), lse ? lse + c * bq : nullptr,
-            workspace_bytes > 0 ? workspace : nullptr, workspace_bytes,
-            static_cast<hipStream_t>(stream));
-        if (e != hipSuccess) return launched(e, "hga_prefill_blocks launch");
+    // The whole prompt is here: every block's summaries (of its keys alone)
+    // and q_bar, then every block's routing against the chunks before it, then
+    // every block's attention, each in one launch over block-major tensors.
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    hipError_t e = hga::launch_summaries_qbar(*plan, k_res, res_tokens, 0, 0, n_blocks, chunk_sum,
+                                              group_sum, table_chunks, q_blocks, 0, n_blocks, qbar,
+                                              st, true);
+    if (e == hipSuccess)
+        e = hga::launch_route_from_qbar(*plan, qbar, 0, n_blocks, chunk_sum, group_sum,
+                                        table_chunks, chunk_idx, group_idx, st, true);
+    if (e == hipSuccess) {
+        // with a workspace the few-unit form may change the order of the sums
+        if (workspace_bytes > 0 && hga::attend_split_applies(*plan) &&
+            hga::attend_few_applies(*plan, n_blocks))
+            e = hga::launch_attend_few(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
+                                       nullptr, k_routed, v_routed, group_idx, out, lse, st, k_res,
+                                       v_res, res_tokens, true);
+        else
+            e = hga::launch_gather_attend(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
+                                          group_idx, k_routed, v_routed, out, lse, nullptr,
+                                          nullptr, st, true);
     }
-    return HGA_OK;
+    return launched(e, "hga_prefill_blocks launch");
 }
 
 hga_status hga_attend(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,

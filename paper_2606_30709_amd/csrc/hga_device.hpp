@@ -70,6 +70,19 @@ struct FastDiv {
     }
 };
 
+// Where query chunk i of head (or (batch, KV head)) h lies among the chunks of
+// a tensor: [head][chunk] of an ordinary call, [chunk][head] of a block-major
+// one.
+struct ChunkMap {
+    int head, chunk;
+    __host__ __device__ int64_t at(int h, int i) const {
+        return static_cast<int64_t>(h) * head + static_cast<int64_t>(i) * chunk;
+    }
+};
+__host__ __device__ inline ChunkMap chunk_map(int n_heads, int n_chunks, bool block_major) {
+    return block_major ? ChunkMap{1, n_heads} : ChunkMap{n_chunks, 1};
+}
+
 __device__ __forceinline__ vec16 load16(const void* p) {
     return *reinterpret_cast<const vec16*>(p);
 }

@@ -65,7 +65,9 @@ inline int middle_count(const hga_params& p, int c) {
 // candidates, with or without the fused group refinement.
 size_t route_lds_bytes(const hga_plan& plan, int n_max, bool groups);
 
-// Kernel launchers; each returns hipSuccess or the launch error.
+// Kernel launchers; each returns hipSuccess or the launch error.  block_major:
+// the call's per-chunk tensors (queries, q_bar, indices, routed buffers, out,
+// lse) are [query chunk][...] instead of [...][query chunk].
 hipError_t launch_build_summaries(const hga_plan& plan, const void* k_rot, int64_t k_tokens,
                                   int k_chunk0, int chunk_begin, int chunk_end, float* chunk_sum,
                                   float* group_sum, int table_chunks, hipStream_t stream);
@@ -82,14 +84,15 @@ hipError_t launch_route(const hga_plan& plan, const void* q_rot, int q_chunk0, i
 hipError_t launch_route_from_qbar(const hga_plan& plan, const float* qbar, int q_chunk0,
                                   int n_q_chunks, const float* chunk_sum, const float* group_sum,
                                   int table_chunks, int32_t* chunk_idx, int32_t* group_idx,
-                                  hipStream_t stream);
+                                  hipStream_t stream, bool block_major = false);
 
 // Summaries of [chunk_begin, chunk_end) and q_bar of the query chunks in one
 // launch (independent work items).
 hipError_t launch_summaries_qbar(const hga_plan& plan, const void* k_rot, int64_t k_tokens,
                                  int k_chunk0, int chunk_begin, int chunk_end, float* chunk_sum,
                                  float* group_sum, int table_chunks, const void* q_rot,
-                                 int q_chunk0, int n_q_chunks, float* qbar, hipStream_t stream);
+                                 int q_chunk0, int n_q_chunks, float* qbar, hipStream_t stream,
+                                 bool block_major = false);
 
 hipError_t launch_route_groups(const hga_plan& plan, const float* qbar, const int32_t* chunk_idx,
                                int q_chunk0, int n_q_chunks, const float* group_sum,
@@ -98,7 +101,7 @@ hipError_t launch_route_groups(const hga_plan& plan, const float* qbar, const in
 hipError_t launch_gather_kv(const hga_plan& plan, const int32_t* group_idx, int q_chunk0,
                             int n_q_chunks, const void* k_src, const void* v_src,
                             int64_t src_tokens, void* k_routed, void* v_routed,
-                            hipStream_t stream);
+                            hipStream_t stream, bool block_major = false);
 
 // Gather of one query chunk's routed groups through a warm LRU cache of
 // groups in device memory (one workgroup per (batch, KV head)).
@@ -151,7 +154,8 @@ hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chun
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* res_slot, void* k_routed, void* v_routed,
                              const int32_t* group_idx, void* out, float* lse, hipStream_t stream,
-                             const void* k_src, const void* v_src, int64_t src_tokens);
+                             const void* k_src, const void* v_src, int64_t src_tokens,
+                             bool block_major = false);
 
 // Backward of the attention (bf16): dq written, dk and dv (fp32, resident
 // layout) accumulated into or (`write`) written over every resident row.
@@ -183,6 +187,6 @@ hipError_t launch_gather_attend(const hga_plan& plan, const void* q_rot, int q_c
                                 int n_q_chunks, const void* k_res, const void* v_res,
                                 int64_t res_tokens, const int32_t* group_idx, void* k_routed,
                                 void* v_routed, void* out, float* lse, hipEvent_t start,
-                                hipEvent_t stop, hipStream_t stream);
+                                hipEvent_t stop, hipStream_t stream, bool block_major = false);
 
 }  // namespace hga

@@ -61,17 +61,18 @@ __device__ __forceinline__ const T* query_chunk_base(const T* q_rot, int b, int 
                     static_cast<int64_t>(i) * 64) * D;
 }
 
-// q_bar of query chunk i of (batch b, KV head j), rows read from HBM.
+// q_bar of query chunk i of the r query heads from head0 on, rows read from HBM.
 template <typename T, int D>
-__device__ __forceinline__ void wave_query_mean(const T* __restrict__ q_rot, int b, int j, int i,
-                                                int n_q_heads, int r, int n_q_chunks,
-                                                float* out) {
+__device__ __forceinline__ void wave_query_mean(const T* __restrict__ q_rot, int head0, int i, int r,
+                                                const ChunkMap& map, float* out) {
     constexpr int V = elem<T>::kVec;
-    const int64_t qtok = static_cast<int64_t>(n_q_chunks) * 64;
-    const T* qbase = query_chunk_base<T, D>(q_rot, b, j, i, n_q_heads, r, n_q_chunks);
+    const T* qbase = q_rot + map.at(head0, i) * 64 * D;
+    const int64_t head_rows = static_cast<int64_t>(map.head) * 64;
     wave_mean_rows<T, D>(
         r * 64,
-        [&](int row, int cv) { return load16(qbase + ((row >> 6) * qtok + (row & 63)) * D + cv * V); },
+        [&](int row, int cv) {
+            return load16(qbase + ((row >> 6) * head_rows + (row & 63)) * D + cv * V);
+        },
         out);
 }
 

@@ -139,13 +139,15 @@ __device__ inline WaveLds carve(unsigned char* base, int d, int n_list, int topk
 // its top K_c.  With kGroups, the same wavefront goes on
 // to group refinement of its chosen chunks (the work of route_groups_kernel,
 // without a second launch or the q_bar/chunk_idx round trip through memory).
+// block_bh: 0, or (q_bar and the indices block-major, [chunk][batch, KV head])
+// the number of (batch, KV head) pairs.
 template <typename T, int D, bool kGroups, bool kQbarIn>
 __global__ __launch_bounds__(256) void route_kernel(
     const T* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const float* __restrict__ chunk_sum,
     const float* __restrict__ group_sum, int table_chunks, float* __restrict__ qbar,
     int32_t* __restrict__ chunk_idx, int32_t* __restrict__ group_idx, int n_q_heads, int n_kv,
     int keep_first, int window, int topk, int topk_groups, int gpc_shift, int units_per_block,
-    size_t wave_bytes) {
+    size_t wave_bytes, int block_bh) {
     constexpr int kThreads = 256;
     constexpr int TB = table_rows(D);       // table rows per LDS block
     constexpr int TS = D + 4;               // padded LDS row stride (floats)
@@ -162,10 +164,9 @@ __global__ __launch_bounds__(256) void route_kernel(
     const int i = first_i + wave;
     const bool active = wave < units_per_block && i < n_q_chunks;
     const int gpc = 1 << gpc_shift;
-    const int b = bh / n_kv, j = bh % n_kv;
     const int r = n_q_heads / n_kv;
     const int c = q_chunk0 + (active ? i : 0);
-    const int64_t unit = static_cast<int64_t>(bh) * n_q_chunks + i;
+    const int64_t unit = chunk_map(block_bh, n_q_chunks, block_bh > 0).at(bh, i);
 
     // Table rows [keep_first, hi) are needed by some wavefront of the group;
     // the descriptor covers exactly those, so loads past them return zeros.
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256) void route_kernel(
             for (int x = lane; x < D; x += 64) L.q[x] = qbar[unit * D + x];
             wave_sync_lds();
         } else {
-            wave_query_mean<T, D>(q_rot, b, j, i, n_q_heads, r, n_q_chunks, L.q);
+            wave_query_mean<T, D>(q_rot, bh * r, i, r, chunk_map(0, n_q_chunks, false), L.q);
             wave_sync_lds();
             if (lane < D / 4) {
                 const float4 v = *reinterpret_cast<const float4*>(L.q + lane * 4);
@@ -587,7 +588,8 @@ __global__ __launch_bounds__(1024) void route_wide_kernel(
     const T* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const float* __restrict__ chunk_sum,
     const float* __restrict__ group_sum, int table_chunks, float* __restrict__ qbar,
     int32_t* __restrict__ chunk_idx, int32_t* __restrict__ group_idx, int n_q_heads, int n_kv,
-    int keep_first, int window, int topk, int topk_groups, int gpc_shift, int big_off) {
+    int keep_first, int window, int topk, int topk_groups, int gpc_shift, int big_off,
+    int block_bh) {
     constexpr int kThreads = 1024;
     constexpr int F4 = D / 4;                     // float4 per table row
     constexpr int TS = D + 4;                     // padded LDS row stride (floats)
@@ -598,8 +600,9 @@ __global__ __launch_bounds__(1024) void route_wide_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int unit = blockIdx.x;
-    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
-    const int b = bh / n_kv, j = bh % n_kv, r = n_q_heads / n_kv;
+    const int bh = block_bh ? unit % block_bh : unit / n_q_chunks;
+    const int i = block_bh ? unit / block_bh : unit % n_q_chunks;
+    const int r = n_q_heads / n_kv;
     const int c = q_chunk0 + i;
     const int gpc = 1 << gpc_shift;
     WaveLds L = carve(smem_raw, D, kGroups ? topk : 0,
@@ -631,7 +634,7 @@ __global__ __launch_bounds__(1024) void route_wide_kernel(
     } else {
         constexpr int V = elem<T>::kVec;
         const int64_t qtok = static_cast<int64_t>(n_q_chunks) * 64;
-        const T* qbase = query_chunk_base<T, D>(q_rot, b, j, i, n_q_heads, r, n_q_chunks);
+        const T* qbase = q_rot + (static_cast<int64_t>(bh) * r * qtok + static_cast<int64_t>(i) * 64) * D;
         // the r heads' 64-token slices, from the first row of head 0 to the
         // last row of head r - 1
         const buf_rsrc q_rsrc = make_rsrc(
@@ -718,7 +721,7 @@ __global__ __launch_bounds__(1024) void route_spread_kernel(
     const float* __restrict__ chunk_sum, const float* __restrict__ group_sum, int table_chunks,
     int32_t* __restrict__ chunk_idx, int32_t* __restrict__ group_idx,
     uint64_t* __restrict__ ws_keys, unsigned* __restrict__ ws_count, int n_kv, int keep_first,
-    int window, int topk, int topk_groups, int gpc_shift, int parts, int big_off) {
+    int window, int topk, int topk_groups, int gpc_shift, int parts, int big_off, int block_bh) {
     constexpr int kThreads = 1024;
     constexpr int F4 = D / 4;                        // float4 per table row
     constexpr int TS = D + 4;                        // padded LDS row stride (floats)
@@ -729,7 +732,8 @@ __global__ __launch_bounds__(1024) void route_spread_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int unit = blockIdx.x / parts, part = blockIdx.x % parts;
-    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
+    const int bh = block_bh ? unit % block_bh : unit / n_q_chunks;
+    const int i = block_bh ? unit / block_bh : unit % n_q_chunks;
     const int c = q_chunk0 + i;
     WaveLds L = carve(smem_raw, D, kGroups ? topk : 0,
                       kGroups && topk_groups > topk ? topk_groups : topk);
@@ -879,7 +883,7 @@ __global__ __launch_bounds__(kLongThreads) void route_long_kernel(
     const T* __restrict__ q_rot, int q_chunk0, int n_q_chunks, const float* __restrict__ chunk_sum,
     const float* __restrict__ group_sum, int table_chunks, float* __restrict__ qbar,
     int32_t* __restrict__ chunk_idx, int32_t* __restrict__ group_idx, int n_q_heads, int n_kv,
-    int keep_first, int window, int topk, int topk_groups, int gpc_shift) {
+    int keep_first, int window, int topk, int topk_groups, int gpc_shift, int block_bh) {
     constexpr int F4 = D / 4;                       // float4 per table row
     constexpr int TS = D + 4;                       // padded LDS row stride (floats)
     constexpr int PF = kLongRows * F4 / kLongThreads;  // float4 per thread per block
@@ -892,8 +896,9 @@ __global__ __launch_bounds__(kLongThreads) void route_long_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int unit = blockIdx.x;
-    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
-    const int b = bh / n_kv, j = bh % n_kv, r = n_q_heads / n_kv;
+    const int bh = block_bh ? unit % block_bh : unit / n_q_chunks;
+    const int i = block_bh ? unit / block_bh : unit % n_q_chunks;
+    const int r = n_q_heads / n_kv;
     const int c = q_chunk0 + i;
     const int gpc = 1 << gpc_shift;
 
@@ -924,7 +929,7 @@ __global__ __launch_bounds__(kLongThreads) void route_long_kernel(
                 *reinterpret_cast<const float4*>(qbar + static_cast<int64_t>(unit) * D + tid * 4);
     } else {
         if (wave == 0) {
-            wave_query_mean<T, D>(q_rot, b, j, i, n_q_heads, r, n_q_chunks, s_q);
+            wave_query_mean<T, D>(q_rot, bh * r, i, r, chunk_map(0, n_q_chunks, false), s_q);
             wave_sync_lds();
             if (lane < D / 4)
                 *reinterpret_cast<float4*>(qbar + static_cast<int64_t>(unit) * D + lane * 4) =
@@ -1073,7 +1078,8 @@ inline WideGeom route_wide_geom(const hga_plan& plan, int n_max, bool groups, bo
 template <typename T, int D, bool kGroups, bool kQbarIn>
 hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                           const float* chunk_sum, const float* group_sum, int table_chunks,
-                          float* qbar, int32_t* chunk_idx, int32_t* group_idx, hipStream_t stream) {
+                          float* qbar, int32_t* chunk_idx, int32_t* group_idx, int block_bh,
+                          hipStream_t stream) {
     const hga_params& p = plan.p;
     const int n_max = middle_count(p, q_chunk0 + n_q_chunks - 1);
     const int units = p.batch * p.n_kv_heads * n_q_chunks;
@@ -1093,7 +1099,7 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
                                table_chunks, chunk_idx, group_idx, plan.route_keys,
                                plan.route_count, p.n_kv_heads, p.keep_first, recent_window(p),
                                p.topk_chunks, p.topk_groups, gpc_shift, parts,
-                               static_cast<int>(wg.big_off));
+                               static_cast<int>(wg.big_off), block_bh);
             return hipGetLastError();
         }
     }
@@ -1105,7 +1111,7 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
                                q_chunk0, n_q_chunks, chunk_sum, group_sum, table_chunks, qbar,
                                chunk_idx, group_idx, p.n_q_heads, p.n_kv_heads, p.keep_first,
                                recent_window(p), p.topk_chunks, p.topk_groups, gpc_shift,
-                               static_cast<int>(wg.big_off));
+                               static_cast<int>(wg.big_off), block_bh);
             return hipGetLastError();
         }
     }
@@ -1114,7 +1120,7 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
                            dim3(kLongThreads), 0, stream, static_cast<const T*>(q_rot), q_chunk0,
                            n_q_chunks, chunk_sum, group_sum, table_chunks, qbar, chunk_idx,
                            group_idx, p.n_q_heads, p.n_kv_heads, p.keep_first, recent_window(p),
-                           p.topk_chunks, p.topk_groups, gpc_shift);
+                           p.topk_chunks, p.topk_groups, gpc_shift, block_bh);
         return hipGetLastError();
     }
     const RouteGeom g = route_geom(plan, n_max, kGroups);
@@ -1125,7 +1131,7 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
                        static_cast<const T*>(q_rot), q_chunk0, n_q_chunks, chunk_sum, group_sum,
                        table_chunks, qbar, chunk_idx, group_idx, p.n_q_heads, p.n_kv_heads,
                        p.keep_first, recent_window(p), p.topk_chunks, p.topk_groups, gpc_shift, upb,
-                       g.wave_bytes);
+                       g.wave_bytes, block_bh);
     return hipGetLastError();
 }
 
@@ -1133,24 +1139,25 @@ template <bool kGroups, bool kQbarIn>
 hipError_t launch_route_any(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                             const float* chunk_sum, const float* group_sum, int table_chunks,
                             float* qbar, int32_t* chunk_idx, int32_t* group_idx,
-                            hipStream_t stream) {
+                            hipStream_t stream, bool block_major = false) {
     const hga_params& p = plan.p;
+    const int block_bh = block_major ? p.batch * p.n_kv_heads : 0;
     if (p.dtype == HGA_F32) {
         if (p.head_dim == 64)
             return launch_route_t<float, 64, kGroups, kQbarIn>(plan, q_rot, q_chunk0, n_q_chunks, chunk_sum,
                                                       group_sum, table_chunks, qbar, chunk_idx,
-                                                      group_idx, stream);
+                                                      group_idx, block_bh, stream);
         return launch_route_t<float, 128, kGroups, kQbarIn>(plan, q_rot, q_chunk0, n_q_chunks, chunk_sum,
                                                    group_sum, table_chunks, qbar, chunk_idx,
-                                                   group_idx, stream);
+                                                   group_idx, block_bh, stream);
     }
     if (p.head_dim == 64)
         return launch_route_t<bf16_t, 64, kGroups, kQbarIn>(plan, q_rot, q_chunk0, n_q_chunks, chunk_sum,
                                                    group_sum, table_chunks, qbar, chunk_idx,
-                                                   group_idx, stream);
+                                                   group_idx, block_bh, stream);
     return launch_route_t<bf16_t, 128, kGroups, kQbarIn>(plan, q_rot, q_chunk0, n_q_chunks, chunk_sum,
                                                 group_sum, table_chunks, qbar, chunk_idx,
-                                                group_idx, stream);
+                                                group_idx, block_bh, stream);
 }
 
 template <int D>
@@ -1206,10 +1213,10 @@ hipError_t launch_route(const hga_plan& plan, const void* q_rot, int q_chunk0, i
 hipError_t launch_route_from_qbar(const hga_plan& plan, const float* qbar, int q_chunk0,
                                   int n_q_chunks, const float* chunk_sum, const float* group_sum,
                                   int table_chunks, int32_t* chunk_idx, int32_t* group_idx,
-                                  hipStream_t stream) {
+                                  hipStream_t stream, bool block_major) {
     return launch_route_any<true, true>(plan, nullptr, q_chunk0, n_q_chunks, chunk_sum, group_sum,
                                         table_chunks, const_cast<float*>(qbar), chunk_idx,
-                                        group_idx, stream);
+                                        group_idx, stream, block_major);
 }
 
 hipError_t launch_route_groups(const hga_plan& plan, const float* qbar, const int32_t* chunk_idx,

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void summaries_qbar_kernel(
     float* __restrict__ chunk_sum, float* __restrict__ group_sum, int table_chunks, int n_bh,
     const float* __restrict__ phase_group, const float* __restrict__ phase_psi, int group,
     int hf_chunk, int n_sum_blocks, const T* __restrict__ q_rot, int n_q_chunks,
-    float* __restrict__ qbar, int n_q_heads, int n_kv) {
+    float* __restrict__ qbar, int n_q_heads, int n_kv, ChunkMap q_map, ChunkMap unit_map) {
     if (static_cast<int>(blockIdx.x) < n_sum_blocks) {
         summaries_body<T, D>(blockIdx.x, n_sum_blocks, k_rot, k_tokens, k_chunk0, chunk_begin,
                              n_chunks, chunk_sum, group_sum, table_chunks, n_bh, phase_group,
@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kThreads) void summaries_qbar_kernel(
     const int unit = (static_cast<int>(blockIdx.x) - n_sum_blocks) * kWaves + (threadIdx.x >> 6);
     if (unit >= n_bh * n_q_chunks) return;
     const int i = unit % n_q_chunks, bh = unit / n_q_chunks;
-    wave_query_mean<T, D>(q_rot, bh / n_kv, bh % n_kv, i, n_q_heads, n_q_heads / n_kv, n_q_chunks,
-                          qbar + static_cast<int64_t>(unit) * D);
+    const int r = n_q_heads / n_kv;
+    wave_query_mean<T, D>(q_rot, bh * r, i, r, q_map, qbar + unit_map.at(bh, i) * D);
 }
 
 template <typename T, int D>
@@ -242,7 +242,7 @@ template <typename T, int D>
 hipError_t launch_sq_t(const hga_plan& plan, const void* k_rot, int64_t k_tokens, int k_chunk0,
                        int chunk_begin, int chunk_end, float* chunk_sum, float* group_sum,
                        int table_chunks, const void* q_rot, int n_q_chunks, float* qbar,
-                       hipStream_t stream) {
+                       bool block_major, hipStream_t stream) {
     using Gm = SumGeom<T, D>;
     const hga_params& p = plan.p;
     const int gpc = p.chunk / p.group;
@@ -260,7 +260,9 @@ hipError_t launch_sq_t(const hga_plan& plan, const void* k_rot, int64_t k_tokens
                        stream, static_cast<const T*>(k_rot), k_tokens, k_chunk0, chunk_begin,
                        n_chunks, chunk_sum, group_sum, table_chunks, n_bh, plan.phase_group,
                        plan.phase_psi, p.group, p.hf_pairs_chunk, static_cast<int>(sum_blocks),
-                       static_cast<const T*>(q_rot), n_q_chunks, qbar, p.n_q_heads, p.n_kv_heads);
+                       static_cast<const T*>(q_rot), n_q_chunks, qbar, p.n_q_heads, p.n_kv_heads,
+                       chunk_map(p.batch * p.n_q_heads, n_q_chunks, block_major),
+                       chunk_map(n_bh, n_q_chunks, block_major));
     return hipGetLastError();
 }
 
@@ -269,25 +271,26 @@ hipError_t launch_sq_t(const hga_plan& plan, const void* k_rot, int64_t k_tokens
 hipError_t launch_summaries_qbar(const hga_plan& plan, const void* k_rot, int64_t k_tokens,
                                  int k_chunk0, int chunk_begin, int chunk_end, float* chunk_sum,
                                  float* group_sum, int table_chunks, const void* q_rot,
-                                 int q_chunk0, int n_q_chunks, float* qbar, hipStream_t stream) {
+                                 int q_chunk0, int n_q_chunks, float* qbar, hipStream_t stream,
+                                 bool block_major) {
     (void)q_chunk0;  // q_bar depends on the query rows only
     const hga_params& p = plan.p;
     if (p.dtype == HGA_F32) {
         if (p.head_dim == 64)
             return launch_sq_t<float, 64>(plan, k_rot, k_tokens, k_chunk0, chunk_begin, chunk_end,
                                           chunk_sum, group_sum, table_chunks, q_rot, n_q_chunks,
-                                          qbar, stream);
+                                          qbar, block_major, stream);
         return launch_sq_t<float, 128>(plan, k_rot, k_tokens, k_chunk0, chunk_begin, chunk_end,
                                        chunk_sum, group_sum, table_chunks, q_rot, n_q_chunks,
-                                       qbar, stream);
+                                       qbar, block_major, stream);
     }
     if (p.head_dim == 64)
         return launch_sq_t<bf16_t, 64>(plan, k_rot, k_tokens, k_chunk0, chunk_begin, chunk_end,
                                        chunk_sum, group_sum, table_chunks, q_rot, n_q_chunks, qbar,
-                                       stream);
+                                       block_major, stream);
     return launch_sq_t<bf16_t, 128>(plan, k_rot, k_tokens, k_chunk0, chunk_begin, chunk_end,
                                     chunk_sum, group_sum, table_chunks, q_rot, n_q_chunks, qbar,
-                                    stream);
+                                    block_major, stream);
 }
 
 hipError_t launch_build_summaries(const hga_plan& plan, const void* k_rot, int64_t k_tokens,
