@@ -328,41 +328,50 @@ void attend_bwd_dq_kernel(
     }
 }
 
-// Zeros over n 16-byte vectors of dk and of dv (a kernel, not a memset: the
-// call may be captured into a graph).
-__global__ __launch_bounds__(256) void bwd_zero_kernel(float4* __restrict__ dk,
-                                                       float4* __restrict__ dv, int64_t n) {
-    const int64_t at = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
+// Before the unit-by-unit key side: the row statistics, and (n > 0) zeros over
+// n 16-byte vectors of dk and of dv (a kernel, not a memset: the call may be
+// captured into a graph).
+template <int D>
+__global__ __launch_bounds__(256) void attend_bwd_begin_kernel(
+    const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ stat, int64_t rows, int stat_blocks, float4* __restrict__ dk,
+    float4* __restrict__ dv, int64_t n) {
+    const int block = blockIdx.x;
+    if (block < stat_blocks) {
+        bwd_row_stat<D>(out, dout, lse, stat, rows, static_cast<int64_t>(block) * 256 + threadIdx.x);
+        return;
+    }
+    const int64_t at = static_cast<int64_t>(block - stat_blocks) * 1024 + threadIdx.x;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
         if (at + u * 256 < n) dk[at + u * 256] = dv[at + u * 256] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void attend_bwd_stat_kernel(const bf16_t* __restrict__ out,
-                                                              const bf16_t* __restrict__ dout,
-                                                              const float* __restrict__ lse,
-                                                              float* __restrict__ stat, int64_t rows) {
-    bwd_row_stat<D>(out, dout, lse, stat, rows,
-                    static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x);
-}
-
-// Whether the key side goes chunk by chunk: always at d64, below eight query
-// heads per KV head at d128, wherever its lists fit.  Whole backward, unit by
-// unit against chunk by chunk (2 x 160 chunks, groups of 16, K_g 12 and 48,
-// us): d64 1 head 653 / 268 and 1540 / 479 (unit by unit: a fused form of it),
-// 4 heads 286 / 231 and 569 / 434, 8 heads 307 / 276 and 597 / 546; d128 2
-// heads 785 / 456 and 1733 / 863, 4 heads 518 / 420 and 1032 / 806, 6 heads
-// 445 / 440 and 892 / 845, 8 heads 517 / 525 and 979 / 1056 (and 32,768
-// tokens, where every unit's rows no longer come from the L2, 3150 / 3500).
-// At d128 and fewer than 32 units the lists' launch is not won back (2 heads x
-// 20 chunks: 46 / 50, x 50 chunks: 87 / 78).
-bool by_chunk(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
+// Whether the key side goes chunk by chunk, wherever its lists fit: by the
+// pace of each form.  Unit by unit, a tile costs its atomics (8 at d64, 13 at
+// d128, in units of 3 and 4 ns of the chip) and one per query head; chunk by
+// chunk, a (unit, chunk) entry costs its query rows (1.13 and 1.75 a query
+// head), and the lists and their longer launch about 25 us more.  Whole
+// backward, unit by unit / chunk by chunk, us, groups of 16 (8), about 0.6
+// chunks a group:
+//   d64, 2 x 160 chunks, K_g 12: 2 heads 92 / 91, 4 heads 105 / 112, 8 heads
+//   130 / 148; K_g 48: 1 head 168 / 104, 4 heads 202 / 191, 8 heads 234 / 297;
+//   8 x 192, K_g 12: 4 heads 410 / 290; 4 x 512, K_g 48: 4 heads 1065 / 902, 8
+//   heads 1352 / 1756; 2 x 45 (8), K_g 19: 2 heads 36 / 48, 4 heads 39 / 67;
+//   6 x 45 (8), K_g 19 of 5 chunks: 3 heads 77 / 66.
+//   d128, 2 x 160, K_g 12: 2 heads 171 / 172, 4 heads 198 / 217; K_g 48: 2
+//   heads 342 / 232, 4 heads 383 / 356, 6 heads 437 / 527, 8 heads 465 / 604;
+//   4 x 512, K_g 48: 4 heads 2157 / 1869, 8 heads 2796 / 3633; 1 x 50, K_g 12:
+//   2 heads 42 / 50, 4 heads 47 / 71.
+// (One head: equal where launches are small, chunk by chunk from there on.)
+bool by_chunk(const hga_plan& plan, int q_chunk0, int n_q_chunks, int fixed, int tiles) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
-    const int64_t units = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks;
-    return (p.head_dim == 64 || r == 1 || (r < 8 && units >= 32)) &&
-           bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
+    const double units = static_cast<double>(p.batch) * p.n_kv_heads * n_q_chunks;
+    const double entries = units * (fixed + std::min(p.topk_chunks, p.topk_groups));
+    const double by_unit = units * tiles * ((p.head_dim == 64 ? 8 : 13) + r);
+    const double chunks = entries * r * (p.head_dim == 64 ? 1.13 : 1.75) + 8500;
+    return (r == 1 || chunks <= by_unit) && bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
 }
 
 template <int D, int KS, int NW>
@@ -391,26 +400,26 @@ hipError_t launch_bwd_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     const int64_t rows = static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks * KT;
     float* stat = dq;
     hipError_t e;
-    if (by_chunk(plan, q_chunk0, n_q_chunks)) {
+    // tiles of the largest working set: the last chunk's visible chunks
+    const int fixed = 1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, window).count;
+    const int tiles = fixed + (p.topk_groups * p.group + KT - 1) / KT;
+    if (by_chunk(plan, q_chunk0, n_q_chunks, fixed, tiles)) {
         e = launch_bwd_chunks(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                               group_idx, out, lse, dout, dq, dk, dv, write, stream);
     } else {
-        if (write) {
-            const int64_t n = static_cast<int64_t>(p.batch) * p.n_kv_heads * res_tokens * (D / 4);
-            hipLaunchKernelGGL(bwd_zero_kernel, dim3(static_cast<unsigned>((n + 1023) / 1024)),
-                               dim3(256), 0, stream, reinterpret_cast<float4*>(dk),
-                               reinterpret_cast<float4*>(dv), n);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL((attend_bwd_stat_kernel<D>),
-                           dim3(static_cast<unsigned>((rows * 8 + 255) / 256)), dim3(256), 0,
+        const int64_t n = write ? static_cast<int64_t>(p.batch) * p.n_kv_heads * res_tokens * (D / 4) : 0;
+        const int64_t stat_blocks = (rows * 8 + 255) / 256, zero_blocks = (n + 1023) / 1024;
+        if (stat_blocks + zero_blocks > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((attend_bwd_begin_kernel<D>),
+                           dim3(static_cast<unsigned>(stat_blocks + zero_blocks)), dim3(256), 0,
                            stream, static_cast<const bf16_t*>(out),
-                           static_cast<const bf16_t*>(dout), lse, stat, rows);
+                           static_cast<const bf16_t*>(dout), lse, stat, rows,
+                           static_cast<int>(stat_blocks), reinterpret_cast<float4*>(dk),
+                           reinterpret_cast<float4*>(dv), n);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         e = launch_bwd_units(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx,
-                             stat, dout, dk, dv, stream);
+                             stat, dout, dk, dv, tiles, stream);
     }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attend_bwd_dq_kernel<D, KS, NW>), grid(items_dq), dim3(NW * 64),

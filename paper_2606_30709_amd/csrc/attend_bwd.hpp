@@ -25,11 +25,12 @@ hipError_t launch_bwd_chunks(const hga_plan& plan, const void* q_rot, int q_chun
                              const void* dout, float* dq, float* dk, float* dv, bool write,
                              hipStream_t stream);
 
-// dk += .., dv += .. unit by unit, from the row statistics.
+// dk += .., dv += .. unit by unit, from the row statistics; at most `tiles` key
+// tiles a unit.
 hipError_t launch_bwd_units(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                             const void* k_res, const void* v_res, int64_t res_tokens,
                             const int32_t* group_idx, const float* stat, const void* dout,
-                            float* dk, float* dv, hipStream_t stream);
+                            float* dk, float* dv, int tiles, hipStream_t stream);
 
 // Workgroup barrier that orders LDS only: waits for this wave's LDS
 // operations, not for its copies or atomics.

@@ -693,7 +693,7 @@ template <int D, int QR, int NS>
 hipError_t launch_units_t(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                           const void* k_res, const void* v_res, int64_t res_tokens,
                           const int32_t* group_idx, const float* stat, const void* dout, float* dk,
-                          float* dv, hipStream_t stream) {
+                          float* dv, int tiles, hipStream_t stream) {
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
@@ -704,9 +704,6 @@ hipError_t launch_units_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
     if (ce != hipSuccess) return ce;
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
     const int window = recent_window(p);
-    // tiles of the largest working set: the last chunk's visible chunks
-    const int tiles = 1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, window).count +
-                      (p.topk_groups * p.group + KT - 1) / KT;
     const int64_t n = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * tiles;
     if (n > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((bwd_unit_kernel<D, QR, NS>),
@@ -725,10 +722,10 @@ hipError_t launch_units_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
 hipError_t launch_bwd_units(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                             const void* k_res, const void* v_res, int64_t res_tokens,
                             const int32_t* group_idx, const float* stat, const void* dout,
-                            float* dk, float* dv, hipStream_t stream) {
+                            float* dk, float* dv, int tiles, hipStream_t stream) {
     return (plan.p.head_dim == 64 ? launch_units_t<64, 64, 2> : launch_units_t<128, 32, 2>)(
         plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens, group_idx, stat, dout, dk, dv,
-        stream);
+        tiles, stream);
 }
 
 bool bwd_chunks_fit(const hga_plan& plan, int q_chunk0, int n_q_chunks) {

@@ -108,6 +108,28 @@ def test_backward_group_id_forms(d, group, kv, ratio, kg, first, last):
         _check(w, q0, _ids(w, q0, rng), seed=kg + q0)
 
 
+@pytest.mark.parametrize("d,group,ratio,kg,first,last", [
+    (64, 16, 2, 12, 1, 0),
+    (64, 8, 3, 21, 2, 3),
+    (64, 32, 7, 5, 1, 1),
+    (128, 16, 2, 9, 1, 2),
+    (128, 8, 4, 13, 1, 0),
+    (128, 32, 5, 4, 2, 1),
+])
+def test_backward_lists_of_several_heads(d, group, ratio, kg, first, last):
+    """Several query heads per KV head in launches large enough for the lists
+    (smaller ones go unit by unit)."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    tiles = 1 + first + max(last, 1) + -(-kg * group // 64)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    batch = -(-8 * n_cu // (21 * tiles))
+    w = W.preset("smalllm").with_(batch=batch, n_q_heads=ratio, n_kv_heads=1, head_dim=d,
+                                  seq_len=64 * 21, group=group, topk_groups=kg, topk_chunks=4,
+                                  keep_first=first, keep_last=last, needle_mode="none")
+    _check(w, 0, _ids(w, 0, np.random.default_rng(d + kg)), seed=kg)
+
+
 @pytest.mark.parametrize("d,chunks,q0", [
     (64, 2050, 2049),    # the lists do not fit one query chunk's dq
     (64, 2050, 2042),    # they fit eight's
