@@ -424,8 +424,8 @@ hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t 
  * attends) and need not hold anything before.  The same sums as
  * hga_attend_backward into zeros, without reading them and without the
  * caller's zeroing.  dk and dv must not overlap each other or any other
- * argument.  Other arguments, requirements and errors as
- * hga_attend_backward. */
+ * argument.  With n_q_chunks = 0 nothing is written.  Other arguments,
+ * requirements and errors as hga_attend_backward. */
 hga_status hga_attend_backward_write(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
                                      int32_t n_q_chunks, const void* k_res, const void* v_res,
                                      int64_t res_tokens, const int32_t* group_idx,

@@ -15,7 +15,7 @@
 // the 608 KB of a 64K decode block's 19 tiles).  Dividing each unit's tiles
 // among workgroups instead (80 of them for the four units of that block) moves
 // less per CU but leaves 10.6 MB of fp32 partial results for a second kernel:
-// HGA_FEW.
+// 19.8 us for that block's attention, against 13.7 here.
 #include <hip/hip_runtime.h>
 #include <math.h>
 

@@ -1076,31 +1076,31 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
         return launch_mfma_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                      res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,
                                      nullptr, stream, k_src, v_src, src_tokens);
+    // Few units: every query tile's workgroup copies the routed rows.  Over
+    // the host link they pass once instead: gathered to the routed buffers, or
+    // to the workspace when there are none and it is large enough (else by the
+    // splits, which copy each row once a unit).
     if (attend_few_applies(plan, n_q_chunks)) {
-        // Every query tile's workgroup copies the routed rows.  Over the host
-        // link they pass once instead: gathered to the routed buffers, or to
-        // the workspace when there are none and it is large enough.
-        if (src_on_host) {
-            const int64_t bytes = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks *
-                                  p.topk_groups * p.group * p.head_dim * 2;
-            void* kr = k_routed;
-            void* vr = v_routed;
-            if (!kr && 2 * bytes <= workspace_bytes) {
-                kr = workspace;
-                vr = static_cast<unsigned char*>(workspace) + bytes;
-            }
-            if (kr) {
-                const hipError_t e = launch_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_src,
-                                                      v_src, src_tokens, kr, vr, stream);
-                if (e != hipSuccess) return e;
-                return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,
-                                         res_tokens, res_slot, kr, vr, group_idx, out, lse,
-                                         stream, nullptr, nullptr, 0);
-            }
+        if (!src_on_host)
+            return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                                     res_slot, k_routed, v_routed, group_idx, out, lse, stream,
+                                     k_src, v_src, src_tokens);
+        const int64_t bytes = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks *
+                              p.topk_groups * p.group * p.head_dim * 2;
+        void* kr = k_routed;
+        void* vr = v_routed;
+        if (!kr && 2 * bytes <= workspace_bytes) {
+            kr = workspace;
+            vr = static_cast<unsigned char*>(workspace) + bytes;
         }
-        return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                                 res_slot, k_routed, v_routed, group_idx, out, lse, stream, k_src,
-                                 v_src, src_tokens);
+        if (kr) {
+            const hipError_t e = launch_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_src,
+                                                  v_src, src_tokens, kr, vr, stream);
+            if (e != hipSuccess) return e;
+            return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                                     res_slot, kr, vr, group_idx, out, lse, stream, nullptr,
+                                     nullptr, 0);
+        }
     }
     return launch_split_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                   res_slot, k_routed, v_routed, group_idx, out, lse,
