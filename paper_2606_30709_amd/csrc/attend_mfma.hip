@@ -1001,32 +1001,34 @@ bool attend_split_applies(const hga_plan& plan) {
     return plan.p.dtype == HGA_BF16 && plan.p.n_q_heads / plan.p.n_kv_heads >= 2;
 }
 
-// Splits for a launch of n_q_chunks query chunks from q_chunk0: enough
-// workgroups to give every compute unit one, at least two key tiles per
-// split, at most what the workspace holds; 1 where the split form does not
-// apply (fp32, one query head per KV head).
+// Most splits a launch of n_q_chunks query chunks takes, however many key
+// tiles its units have: enough workgroups to give every compute unit one, at
+// most what the workspace holds; 1 where the split form does not apply (fp32,
+// one query head per KV head).
+int attend_most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_bytes) {
+    const hga_params& p = plan.p;
+    if (!attend_split_applies(plan)) return 1;
+    const int r = p.n_q_heads / p.n_kv_heads;
+    const int qt_per_wg = p.head_dim == 128 ? kD128Waves : 4;
+    const int wg_per_unit = (2 * r + qt_per_wg - 1) / qt_per_wg;
+    const int64_t items = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * wg_per_unit;
+    int64_t want = (plan.n_cu + items - 1) / items;
+    want = want < kMaxSplit ? want : kMaxSplit;
+    const int64_t per = attend_split_bytes_per_split(plan, n_q_chunks);
+    const int64_t fit = per > 0 ? workspace_bytes / per : 0;
+    return static_cast<int>(want < fit ? want : fit);
+}
+
+// Splits for a launch of n_q_chunks query chunks from q_chunk0: the most, with
+// at least two key tiles per split.
 static int choose_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks,
                          int64_t workspace_bytes) {
     const hga_params& p = plan.p;
-    const int r = p.n_q_heads / p.n_kv_heads;
-    int n_split = 1;
-    if (attend_split_applies(plan)) {
-        // enough workgroups to give every compute unit one, at least two key
-        // tiles per split, at most what the workspace holds
-        const int qt_per_wg = p.head_dim == 128 ? kD128Waves : 4;
-        const int wg_per_unit = (2 * r + qt_per_wg - 1) / qt_per_wg;
-        const int64_t items = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * wg_per_unit;
-        const int c_last = q_chunk0 + n_q_chunks - 1;
-        const int n_rt = (p.topk_groups * p.group + KT - 1) / KT;
-        const int n_tiles = 1 + VisibleChunks(c_last, p.keep_first, recent_window(p)).count + n_rt;
-        int64_t want = (plan.n_cu + items - 1) / items;
-        want = want < (n_tiles + 1) / 2 ? want : (n_tiles + 1) / 2;
-        want = want < kMaxSplit ? want : kMaxSplit;
-        const int64_t per = attend_split_bytes_per_split(plan, n_q_chunks);
-        const int64_t fit = per > 0 ? workspace_bytes / per : 0;
-        n_split = static_cast<int>(want < fit ? want : fit);
-    }
-    return n_split;
+    const int most = attend_most_splits(plan, n_q_chunks, workspace_bytes);
+    const int n_rt = (p.topk_groups * p.group + KT - 1) / KT;
+    const int n_tiles =
+        1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, recent_window(p)).count + n_rt;
+    return most < (n_tiles + 1) / 2 ? most : (n_tiles + 1) / 2;
 }
 
 hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_chunk0,
@@ -1043,8 +1045,8 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
     if (attend_few_applies(plan, n_q_chunks))
         return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                  res_slot, const_cast<void*>(k_routed),
-                                 const_cast<void*>(v_routed), group_idx, out, lse, stream, nullptr,
-                                 nullptr, 0);
+                                 const_cast<void*>(v_routed), group_idx, out, lse, n_split, stream,
+                                 nullptr, nullptr, 0);
     return launch_split_any<false>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                    res_slot, k_routed, v_routed, group_idx, out, lse,
                                    static_cast<float*>(workspace), n_split, stream);
@@ -1083,8 +1085,8 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
     if (attend_few_applies(plan, n_q_chunks)) {
         if (!src_on_host)
             return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                                     res_slot, k_routed, v_routed, group_idx, out, lse, stream,
-                                     k_src, v_src, src_tokens);
+                                     res_slot, k_routed, v_routed, group_idx, out, lse, n_split,
+                                     stream, k_src, v_src, src_tokens);
         const int64_t bytes = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks *
                               p.topk_groups * p.group * p.head_dim * 2;
         void* kr = k_routed;
@@ -1098,7 +1100,7 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                                   v_src, src_tokens, kr, vr, stream);
             if (e != hipSuccess) return e;
             return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                                     res_slot, kr, vr, group_idx, out, lse, stream, nullptr,
+                                     res_slot, kr, vr, group_idx, out, lse, n_split, stream, nullptr,
                                      nullptr, 0);
         }
     }

@@ -903,11 +903,11 @@ hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_
                                         table_chunks, chunk_idx, group_idx, st, true);
     if (e == hipSuccess) {
         // with a workspace the few-unit form may change the order of the sums
-        if (workspace_bytes > 0 && hga::attend_split_applies(*plan) &&
-            hga::attend_few_applies(*plan, n_blocks))
+        const int most = hga::attend_most_splits(*plan, 1, workspace_bytes);
+        if (most > 1 && hga::attend_few_applies(*plan, n_blocks))
             e = hga::launch_attend_few(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
-                                       nullptr, k_routed, v_routed, group_idx, out, lse, st, k_res,
-                                       v_res, res_tokens, true);
+                                       nullptr, k_routed, v_routed, group_idx, out, lse, most, st,
+                                       k_res, v_res, res_tokens, true);
         else
             e = hga::launch_gather_attend(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
                                           group_idx, k_routed, v_routed, out, lse, nullptr,

@@ -146,16 +146,21 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
                                float* lse, void* workspace, int64_t workspace_bytes,
                                hipStream_t stream);
 
-// The attention of a few units in one launch: every key of a query tile in one
-// workgroup.  Routed rows from k_routed / v_routed, or (k_src given) gathered
-// from k_src / v_src and written to k_routed / v_routed when those are given.
+// Most splits of a launch of n_q_chunks query chunks, by compute units and workspace.
+int attend_most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_bytes);
+
+// The split form for a few units in one launch, bit for bit: a workgroup takes
+// every key of a query tile, a wavefront a split of them.  Routed rows from
+// k_routed / v_routed, or (k_src given) gathered from k_src / v_src and written
+// to k_routed / v_routed when those are given.  block_major: every query chunk
+// stands for a call of its own, with at most n_split splits.
 bool attend_few_applies(const hga_plan& plan, int n_q_chunks);
 hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* res_slot, void* k_routed, void* v_routed,
-                             const int32_t* group_idx, void* out, float* lse, hipStream_t stream,
-                             const void* k_src, const void* v_src, int64_t src_tokens,
-                             bool block_major = false);
+                             const int32_t* group_idx, void* out, float* lse, int n_split,
+                             hipStream_t stream, const void* k_src, const void* v_src,
+                             int64_t src_tokens, bool block_major = false);
 
 // Backward of the attention (bf16): dq written, dk and dv (fp32, resident
 // layout) accumulated into or (`write`) written over every resident row.

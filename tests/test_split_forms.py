@@ -1,0 +1,138 @@
+"""The split attention's two kernels: workgroups that each leave a partial
+result for a merge kernel, and (launches of a few query tiles) one workgroup
+for all splits of a query tile.  They form the same sums in the same order, so
+no call's bits depend on which of them it takes."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_30709_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int16 if t.dtype == torch.bfloat16 else torch.int32)
+
+
+def _same(a, b):
+    return torch.equal(_bits(a), _bits(b))
+
+
+class _Case:
+    """Random inputs of `n` query chunks after `q0`, with ids of the causal
+    past, some padded, repeated or in the future."""
+
+    def __init__(self, d, kv, ratio, group, kg, first, last, q0, n, batch=1, seed=0):
+        if not torch.cuda.is_available():
+            pytest.skip("needs a GPU")
+        from paper_2606_30709_amd import hga
+        self.hga = hga
+        self.w = w = W.preset("qwen32k").with_(
+            batch=batch, n_q_heads=kv * ratio, n_kv_heads=kv, head_dim=d, seq_len=64 * (q0 + n),
+            group=group, topk_groups=kg, topk_chunks=min(kg, 8), keep_first=first, keep_last=last,
+            needle_mode="none")
+        self.plan, self.q0, self.n = hga.Plan.for_workload(w), q0, n
+        g = torch.Generator().manual_seed(seed)
+        bf = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16).cuda()  # noqa: E731
+        self.q = bf(batch, kv * ratio, n * 64, d) * 3
+        self.k, self.v = bf(batch, kv, 64 * (q0 + n), d), bf(batch, kv, 64 * (q0 + n), d)
+        rng = np.random.default_rng(seed)
+        gpc = 64 // group
+        gi = np.full((batch, kv, n, kg), -1, dtype=np.int32)
+        for i in range(n):
+            c = q0 + i
+            if c:
+                gi[:, :, i] = np.sort(rng.integers(0, c * gpc, size=(batch, kv, kg)), axis=-1)
+                if i % 3 == 1:
+                    gi[:, :, i, kg // 2:] = -1
+                if i % 4 == 2:
+                    gi[:, :, i, 0] = c * gpc
+        self.gi = torch.from_numpy(gi).cuda()
+        self.kr = torch.full((batch, kv, n, kg * group, d), float("nan"), dtype=torch.bfloat16,
+                             device="cuda")
+        self.vr = self.kr.clone()
+        hga.hga_gather_kv(self.plan, self.gi, q0, self.k, self.v, self.kr, self.vr)
+
+    def split_bytes(self, n):
+        """Bytes of one split of n query chunks."""
+        return self.hga.hga_attend_split_workspace(self.plan, n) // 16
+
+    def attend_split(self, i, n, workspace_bytes):
+        s = slice(i * 64, (i + n) * 64)
+        q = self.q[:, :, s].contiguous()
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+        ws = torch.full((workspace_bytes // 4,), float("nan"), device="cuda")
+        self.hga.hga_attend_split(self.plan, q, self.q0 + i, self.k, self.v,
+                                  self.kr[:, :, i:i + n].contiguous(),
+                                  self.vr[:, :, i:i + n].contiguous(),
+                                  self.gi[:, :, i:i + n].contiguous(), out, ws, lse)
+        torch.cuda.synchronize()
+        return out, lse
+
+
+@pytest.mark.parametrize("d,kv,ratio,group,kg,first,last,q0,n", [
+    (128, 1, 2, 16, 9, 1, 0, 9, 70),       # 3 splits of a 5-tile unit
+    (128, 1, 16, 8, 37, 2, 3, 6, 9),       # 6 splits; routed rows end in a half tile
+    (128, 2, 8, 32, 23, 1, 2, 5, 9),       # 8 splits
+    (64, 1, 2, 16, 7, 1, 2, 4, 66),        # 3 splits
+    (64, 1, 3, 8, 22, 1, 1, 3, 45),        # 3 splits, heads beyond one workgroup
+    (64, 1, 16, 32, 6, 1, 0, 3, 9),        # 3 splits, eight workgroups a unit
+])
+def test_few_units_form_has_the_split_forms_bits(d, kv, ratio, group, kg, first, last, q0, n):
+    """A call with more query tiles than compute units takes the workgroup
+    form with the merge kernel; its chunks one by one take the other.  The
+    split counts agree (two tiles a split bound both)."""
+    t = _Case(d, kv, ratio, group, kg, first, last, q0, n)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert 2 * kv * ratio * n > n_cu >= 2 * kv * ratio
+    tiles = 1 + len(t.hga.hga_visible_chunks(t.plan.params, q0 + n - 1)) + -(-kg * group // 64)
+    assert tiles == 1 + len(t.hga.hga_visible_chunks(t.plan.params, q0)) + -(-kg * group // 64)
+    most = -(-n_cu // (kv * n * -(-2 * ratio // (8 if d == 128 else 4))))
+    assert 1 < (tiles + 1) // 2 <= most
+    out, lse = t.attend_split(0, n, t.hga.hga_attend_split_workspace(t.plan, n))
+    assert not out.isnan().any() and not lse.isnan().any()
+    for i in range(n):
+        o1, l1 = t.attend_split(i, 1, t.hga.hga_attend_split_workspace(t.plan, 1))
+        s = slice(i * 64, (i + 1) * 64)
+        assert _same(o1, out[:, :, s]) and _same(l1, lse[:, :, s]), i
+
+
+@pytest.mark.parametrize("d,ratio,group,kg,splits", [
+    (128, 2, 16, 32, 2),     # two splits' workspace holds no 512 routed rows
+    (128, 2, 8, 512, 9),
+    (128, 2, 8, 512, 10),
+    (128, 2, 8, 509, 11),
+    (128, 2, 8, 512, 16),
+    (64, 2, 16, 40, 2),
+    (64, 2, 8, 509, 9),
+    (64, 2, 8, 512, 16),
+])
+def test_host_source_bits_without_room_for_the_routed_rows(d, ratio, group, kg, splits):
+    """From host memory without routed buffers, and with a workspace that holds
+    the splits but not the rows, the output is still the one with buffers and
+    that of hga_gather_kv and hga_attend_split, bit for bit."""
+    t = _Case(d, 2, ratio, group, kg, 1, 1, 20, 2, batch=2, seed=kg)
+    hga, plan = t.hga, t.plan
+    kh, vh = t.k.cpu().pin_memory(), t.v.cpu().pin_memory()
+    for i, n in ((1, 1), (0, 2)):
+        nbytes = splits * t.split_bytes(n)
+        assert nbytes < 2 * t.kr[:, :, :n].numel() * 2
+        q = t.q[:, :, i * 64:(i + n) * 64].contiguous()
+        gi = t.gi[:, :, i:i + n].contiguous()
+        want = t.attend_split(i, n, nbytes)
+        for buffers in (False, True):
+            kr, vr = (torch.full_like(x[:, :, i:i + n], float("nan")) for x in (t.kr, t.vr))
+            out = torch.full_like(q, float("nan"))
+            lse = torch.full(q.shape[:3], float("nan"), device="cuda")
+            ws = torch.empty(nbytes // 4, device="cuda")
+            hga.hga_gather_attend_split(plan, q, t.q0 + i, t.k, t.v, kh, vh, gi,
+                                        kr if buffers else None, vr if buffers else None, out, ws,
+                                        lse, src_on_host=True)
+            torch.cuda.synchronize()
+            assert _same(out, want[0]) and _same(lse, want[1]), (i, n, buffers)
+            if buffers:
+                assert _same(kr, t.kr[:, :, i:i + n]) and _same(vr, t.vr[:, :, i:i + n])
