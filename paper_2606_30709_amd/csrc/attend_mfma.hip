@@ -1005,7 +1005,7 @@ bool attend_split_applies(const hga_plan& plan) {
 // tiles its units have: enough workgroups to give every compute unit one, at
 // most what the workspace holds; 1 where the split form does not apply (fp32,
 // one query head per KV head).
-int attend_most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_bytes) {
+static int most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_bytes) {
     const hga_params& p = plan.p;
     if (!attend_split_applies(plan)) return 1;
     const int r = p.n_q_heads / p.n_kv_heads;
@@ -1021,10 +1021,9 @@ int attend_most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_b
 
 // Splits for a launch of n_q_chunks query chunks from q_chunk0: the most, with
 // at least two key tiles per split.
-static int choose_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks,
-                         int64_t workspace_bytes) {
+int attend_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks, int64_t workspace_bytes) {
     const hga_params& p = plan.p;
-    const int most = attend_most_splits(plan, n_q_chunks, workspace_bytes);
+    const int most = most_splits(plan, n_q_chunks, workspace_bytes);
     const int n_rt = (p.topk_groups * p.group + KT - 1) / KT;
     const int n_tiles =
         1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, recent_window(p)).count + n_rt;
@@ -1037,7 +1036,7 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
                                const void* v_routed, const int32_t* group_idx, void* out,
                                float* lse, void* workspace, int64_t workspace_bytes,
                                hipStream_t stream) {
-    const int n_split = choose_splits(plan, q_chunk0, n_q_chunks, workspace_bytes);
+    const int n_split = attend_splits(plan, q_chunk0, n_q_chunks, workspace_bytes);
     if (n_split <= 1)
         return launch_attend(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                              res_slot, k_routed, v_routed, group_idx, out, lse, nullptr, nullptr,
@@ -1073,7 +1072,7 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                   res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,
                                   nullptr, stream, k_src, v_src, src_tokens);
     }
-    const int n_split = choose_splits(plan, q_chunk0, n_q_chunks, workspace_bytes);
+    const int n_split = attend_splits(plan, q_chunk0, n_q_chunks, workspace_bytes);
     if (n_split <= 1)
         return launch_mfma_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                      res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,

@@ -894,6 +894,10 @@ hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_
     // The whole prompt is here: every block's summaries (of its keys alone)
     // and q_bar, then every block's routing against the chunks before it, then
     // every block's attention, each in one launch over block-major tensors.
+    // With a workspace each block's output is that of a split attention of its
+    // own (hga_block_step's, bit for bit); where that has one split, and
+    // without a workspace, it is the bulk prefill's.
+    const int n_split = hga::attend_splits(*plan, n_blocks - 1, 1, workspace_bytes);
     const hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hga::launch_summaries_qbar(*plan, k_res, res_tokens, 0, 0, n_blocks, chunk_sum,
                                               group_sum, table_chunks, q_blocks, 0, n_blocks, qbar,
@@ -901,18 +905,14 @@ hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_
     if (e == hipSuccess)
         e = hga::launch_route_from_qbar(*plan, qbar, 0, n_blocks, chunk_sum, group_sum,
                                         table_chunks, chunk_idx, group_idx, st, true);
-    if (e == hipSuccess) {
-        // with a workspace the few-unit form may change the order of the sums
-        const int most = hga::attend_most_splits(*plan, 1, workspace_bytes);
-        if (most > 1 && hga::attend_few_applies(*plan, n_blocks))
-            e = hga::launch_attend_few(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
-                                       nullptr, k_routed, v_routed, group_idx, out, lse, most, st,
-                                       k_res, v_res, res_tokens, true);
-        else
-            e = hga::launch_gather_attend(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
-                                          group_idx, k_routed, v_routed, out, lse, nullptr,
-                                          nullptr, st, true);
-    }
+    if (e == hipSuccess)
+        e = n_split > 1
+                ? hga::launch_attend_few(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
+                                         nullptr, k_routed, v_routed, group_idx, out, lse, n_split,
+                                         st, k_res, v_res, res_tokens, true)
+                : hga::launch_gather_attend(*plan, q_blocks, 0, n_blocks, k_res, v_res, res_tokens,
+                                            group_idx, k_routed, v_routed, out, lse, nullptr,
+                                            nullptr, st, true);
     return launched(e, "hga_prefill_blocks launch");
 }
 

@@ -146,8 +146,9 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
                                float* lse, void* workspace, int64_t workspace_bytes,
                                hipStream_t stream);
 
-// Most splits of a launch of n_q_chunks query chunks, by compute units and workspace.
-int attend_most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_bytes);
+// Splits of a launch of n_q_chunks query chunks from q_chunk0 (below two: the
+// unsplit attention).
+int attend_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks, int64_t workspace_bytes);
 
 // The split form for a few units in one launch, bit for bit: a workgroup takes
 // every key of a query tile, a wavefront a split of them.  Routed rows from

@@ -136,3 +136,60 @@ def test_host_source_bits_without_room_for_the_routed_rows(d, ratio, group, kg, 
             assert _same(out, want[0]) and _same(lse, want[1]), (i, n, buffers)
             if buffers:
                 assert _same(kr, t.kr[:, :, i:i + n]) and _same(vr, t.vr[:, :, i:i + n])
+
+
+@pytest.mark.parametrize("key,kw,splits", [
+    # one tile of routed rows: block 0 has one split, the others two or three
+    ("qwen32k", dict(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=64 * 12, topk_groups=4,
+                     topk_chunks=3), 16),
+    # more query tiles than compute units, a workspace for five splits, ragged rows
+    ("qwen32k", dict(n_q_heads=16, n_kv_heads=2, seq_len=64 * 24, topk_groups=45, keep_last=3), 5),
+    # up to nine and ten splits, one a wavefront
+    ("qwen32k", dict(n_q_heads=8, n_kv_heads=2, seq_len=64 * 33, group=32, topk_groups=29,
+                     keep_last=1), 16),
+    # up to sixteen, two a wavefront
+    ("qwen32k", dict(n_q_heads=8, n_kv_heads=4, seq_len=64 * 40, group=32, topk_chunks=40,
+                     topk_groups=61), 16),
+    ("smalllm", dict(batch=2, n_q_heads=6, n_kv_heads=2, seq_len=64 * 21, group=8, topk_groups=21,
+                     topk_chunks=4), 16),
+    ("smalllm", dict(batch=1, n_q_heads=16, n_kv_heads=1, seq_len=64 * 40, group=32,
+                     topk_chunks=40, topk_groups=60), 16),
+    # below two splits, without a workspace, one head per KV head, fp32: unsplit
+    ("qwen32k", dict(n_q_heads=8, n_kv_heads=2, seq_len=64 * 9, topk_groups=9), 1),
+    ("smalllm", dict(batch=1, n_q_heads=4, n_kv_heads=2, seq_len=64 * 9), 0),
+    ("smalllm", dict(batch=2, n_q_heads=2, n_kv_heads=2, seq_len=64 * 9), 16),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2), 16),
+])
+def test_prefill_blocks_has_block_steps_bits(key, kw, splits):
+    """hga_prefill_blocks writes what hga_block_step writes for each block in
+    order, bit for bit, with workspaces of any size; without a split that is
+    the bulk prefill."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2606_30709_amd import hga
+    from paper_2606_30709_amd.pipeline import BlockPrefillPipeline, PrefillPipeline
+    w = W.preset(key).with_(needle_mode="none", **kw)
+    inp = W.generate(w)
+    blk = BlockPrefillPipeline(w, inp)
+    if splits:
+        nbytes = hga.hga_attend_split_workspace(blk.plan, 1) // 16 * splits
+        blk.attend_ws = torch.full((nbytes // 4,), float("nan"), device="cuda")
+    names = ("qbar", "chunk_idx", "group_idx", "k_routed", "v_routed", "out", "lse")
+    for x in ("qbar", "k_routed", "v_routed", "out", "lse", "chunk_sum", "group_sum"):
+        getattr(blk, x).fill_(float("nan"))
+    blk.step()
+    step = {x: torch.zeros_like(getattr(blk, x)) for x in names}
+    cs, gs = torch.full_like(blk.chunk_sum, float("nan")), torch.full_like(blk.group_sum, float("nan"))
+    for c in range(w.n_chunks):
+        hga.hga_block_step(blk.plan, blk.q_blocks[c], c, blk.k, blk.v, cs, gs,
+                           *(step[x][c] for x in names), workspace=blk.attend_ws)
+    torch.cuda.synchronize()
+    assert _same(cs, blk.chunk_sum) and _same(gs, blk.group_sum)
+    for x in names:
+        for c in range(w.n_chunks):
+            assert _same(getattr(blk, x)[c], step[x][c]), (x, c)
+    if splits < 2 or w.gqa_ratio == 1 or w.dtype == "f32":
+        bulk = PrefillPipeline(w, inp)
+        bulk.step()
+        out = bulk.out.view(w.batch, w.n_q_heads, w.n_chunks, 64, w.head_dim).permute(2, 0, 1, 3, 4)
+        assert _same(blk.out, out)
