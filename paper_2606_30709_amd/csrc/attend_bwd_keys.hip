@@ -27,6 +27,7 @@
 #include <algorithm>
 
 #include "attend_bwd.hpp"
+#include "bwd_lists.hpp"
 #include "attend_common.hpp"
 #include "hga_internal.hpp"
 #include "lds_copy.hpp"
@@ -41,17 +42,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;    // tokens per chunk
 constexpr int kXcds = 8;
-constexpr int kIndexThreads = 1024;
-
-// A list entry: query unit, its opened groups of the chunk (bit per group),
-// and whether the chunk is the unit's own (causal mask).
-constexpr int kUnitBits = 22, kMaskShift = 22;
-constexpr uint32_t kCausal = 1u << 30;
-static_assert(kBwdIndexChunks <= 1 << kUnitBits, "unit ids");
-// An item: x = chunk | entries << 15 | (part of a cut list) << 30, y = first
-// entry.
-constexpr int kCountShift = 15;
-static_assert(kBwdIndexChunks <= 1 << kCountShift, "chunk ids");
 
 // The tables of one (batch, KV head), `stride` ints apart.
 struct Index {
@@ -64,47 +54,6 @@ struct Index {
         return reinterpret_cast<uint32_t*>(items(bh) + cap_items);
     }
 };
-
-// Calls f(chunk, entry) for every entry of the (batch, KV head), the work
-// spread over the workgroup: slot 0 of unit i is its own chunk, then its
-// visible chunks, then its routed groups, where a run of ascending groups of
-// one chunk makes one entry (any other order, and repeated ids, make several).
-template <typename F>
-__device__ __forceinline__ void each_entry(const int32_t* __restrict__ gid, int nq, int q_chunk0,
-                                           int keep_first, int window, int topk, int gpc_shift,
-                                           FastDiv per, F f) {
-    const int fixed = per.d - topk;
-    const int gpc = 1 << gpc_shift;
-    for (uint32_t idx = threadIdx.x; idx < nq * per.d; idx += kIndexThreads) {
-        const int i = per.div(idx), k = idx - i * per.d;
-        const int c = q_chunk0 + i;
-        const uint32_t all = ((1u << gpc) - 1) << kMaskShift;
-        if (k == 0) {
-            f(c, static_cast<uint32_t>(i) | all | kCausal);
-        } else if (k < fixed) {
-            const VisibleChunks vis(c, keep_first, window);
-            if (k - 1 < vis.count) f(vis.chunk(k - 1), static_cast<uint32_t>(i) | all);
-        } else {
-            const int32_t* g = gid + static_cast<int64_t>(i) * topk;
-            const int s = k - fixed;
-            const int lim = c << gpc_shift;
-            auto valid = [&](int x) { return x >= 0 && x < lim; };
-            const int g0 = g[s];
-            if (!valid(g0)) continue;
-            const int chunk = g0 >> gpc_shift;
-            const int before = s > 0 ? g[s - 1] : -1;
-            if (valid(before) && (before >> gpc_shift) == chunk && before < g0) continue;
-            uint32_t mask = 1u << (g0 & (gpc - 1));
-            for (int last = g0, t = s + 1; t < topk; ++t) {
-                const int gt = g[t];
-                if (!valid(gt) || (gt >> gpc_shift) != chunk || gt <= last) break;
-                mask |= 1u << (gt & (gpc - 1));
-                last = gt;
-            }
-            f(chunk, static_cast<uint32_t>(i) | mask << kMaskShift);
-        }
-    }
-}
 
 // The lists and the row statistics in one launch (neither needs the other):
 // the first n_bh workgroups invert one (batch, KV head) each, bound by their
@@ -121,52 +70,18 @@ __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
         return;
     }
     extern __shared__ int s_cnt[];  // [n_chunks]
-    __shared__ int s_sum[2][kIndexThreads / 64];
-    const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t* gid = group_idx + static_cast<int64_t>(bh) * nq * topk;
-    for (int x = tid; x < n_chunks; x += kIndexThreads) s_cnt[x] = 0;
-    __syncthreads();
-    each_entry(gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
-               [&](int chunk, uint32_t) { atomicAdd(&s_cnt[chunk], 1); });
-    __syncthreads();
-    // exclusive sums of the entries and of the segments, a run of chunks per thread
-    const int run = (n_chunks + kIndexThreads - 1) / kIndexThreads;
-    const int lo = min(tid * run, n_chunks), hi = min(lo + run, n_chunks);
-    int n_ent = 0, n_seg = 0;
-    for (int x = lo; x < hi; ++x) {
-        n_ent += s_cnt[x];
-        n_seg += (s_cnt[x] + seg - 1) / seg;
-    }
-    int at_ent = wave_incl_scan_add(n_ent), at_seg = wave_incl_scan_add(n_seg);
-    if (lane == 63) {
-        s_sum[0][wave] = at_ent;
-        s_sum[1][wave] = at_seg;
-    }
-    __syncthreads();
-    at_ent -= n_ent;
-    at_seg -= n_seg;
-    for (int w = 0; w < wave; ++w) {
-        at_ent += s_sum[0][w];
-        at_seg += s_sum[1][w];
-    }
-    int2* items = ix.items(bh);
-    for (int x = lo; x < hi; ++x) {
-        const int n = s_cnt[x];
-        s_cnt[x] = at_ent;  // the fill's cursor
-        if (clear) clear[static_cast<int64_t>(bh) * n_chunks + x] = n == 0 || n > seg;
-        for (int o = 0; o < n; o += seg)
-            items[at_seg++] = make_int2(x | min(seg, n - o) << kCountShift | (n > seg) << 30,
-                                        at_ent + o);
-        at_ent += n;
-    }
-    // the unused items have no entries
-    if (tid == kIndexThreads - 1) s_sum[0][0] = at_seg;
-    __syncthreads();
-    for (int x = s_sum[0][0] + tid; x < ix.cap_items; x += kIndexThreads) items[x] = make_int2(0, 0);
-    __syncthreads();
-    uint32_t* entries = ix.entries(bh);
-    each_entry(gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
-               [&](int chunk, uint32_t e) { entries[atomicAdd(&s_cnt[chunk], 1)] = e; });
+    __shared__ BwdListsScratch scratch;
+    const int bh = blockIdx.x;
+    struct Workgroup {
+        __device__ int thread() const { return threadIdx.x; }
+        __device__ void sync() const { __syncthreads(); }
+        __device__ int add(int* at, int x) const { return atomicAdd(at, x); }
+        __device__ int scan(int x) const { return wave_incl_scan_add(x); }
+    };
+    build_bwd_lists(Workgroup{}, group_idx + static_cast<int64_t>(bh) * nq * topk, nq, q_chunk0,
+                    keep_first, window, topk, gpc_shift, per, n_chunks, seg, ix.items(bh),
+                    ix.cap_items, ix.entries(bh),
+                    clear ? clear + static_cast<int64_t>(bh) * n_chunks : nullptr, s_cnt, scratch);
 }
 
 // For a call that writes dk and dv: zeros in the rows of the chunks that the

@@ -65,8 +65,8 @@ struct FastDiv {
         while ((uint32_t(1) << s) < d) ++s;
         m = static_cast<uint32_t>(((uint64_t(1) << 32) * ((uint64_t(1) << s) - d)) / d + 1);
     }
-    __device__ __forceinline__ uint32_t div(uint32_t n) const {
-        return (__umulhi(n, m) + n) >> s;
+    __host__ __device__ uint32_t div(uint32_t n) const {
+        return (static_cast<uint32_t>((static_cast<uint64_t>(n) * m) >> 32) + n) >> s;
     }
 };
 
