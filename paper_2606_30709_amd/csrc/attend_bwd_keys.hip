@@ -2,7 +2,7 @@
 // chunk: every query unit that attends a key chunk (its own, the recent
 // window's, everybody for a sink, and the units that opened some of its
 // groups) passes by the chunk's keys, whose dK and dV stay in registers and
-// are added to memory once.
+// are written or (atomically) added to memory once.
 //
 // Unit-major accumulation adds 64 x D x 2 floats with atomics for every
 // (unit, key tile) pair; with one query head per KV head that is one atomic
@@ -361,21 +361,14 @@ void bwd_chunk_kernel(
                         e & lane_bit ? 0.f : -INFINITY};
     });
 
-    // The chunk's only segment adds in place, or writes (nobody else touches
-    // its rows in this launch); the segments of a cut list add atomically (to
-    // rows that bwd_clear_kernel zeroed, when the call writes).
+    // In a call that writes, the chunk's only segment writes (nobody else
+    // touches its rows in this launch) and the segments of a cut list add to
+    // rows that bwd_clear_kernel zeroed.  A call that adds does so atomically
+    // throughout: another may be adding to the same rows.
     const float ksc = 1.0f / sqrtf(static_cast<float>(D));
     const int64_t at0 = (static_cast<int64_t>(bh) * res_tokens + static_cast<int64_t>(chunk) * KT +
                          wave * 16 + g4 * 4) * D + l16;
-    if (shared) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                unsafeAtomicAdd(dk + at0 + x * D + nb * 16, ak[nb][x] * ksc);
-                unsafeAtomicAdd(dv + at0 + x * D + nb * 16, av[nb][x]);
-            }
-    } else if (write) {
+    if (write && !shared) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -384,20 +377,12 @@ void bwd_chunk_kernel(
                 __builtin_nontemporal_store(av[nb][x], dv + at0 + x * D + nb * 16);
             }
     } else {
-        float ok[NB][4], ov[NB][4];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                ok[nb][x] = dk[at0 + x * D + nb * 16];
-                ov[nb][x] = dv[at0 + x * D + nb * 16];
-            }
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                dk[at0 + x * D + nb * 16] = fmaf(ak[nb][x], ksc, ok[nb][x]);
-                dv[at0 + x * D + nb * 16] = ov[nb][x] + av[nb][x];
+                unsafeAtomicAdd(dk + at0 + x * D + nb * 16, ak[nb][x] * ksc);
+                unsafeAtomicAdd(dv + at0 + x * D + nb * 16, av[nb][x]);
             }
     }
 }

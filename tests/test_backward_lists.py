@@ -144,3 +144,52 @@ def test_backward_few_query_chunks_after_a_long_history(d, chunks, q0):
     rng = np.random.default_rng(chunks + q0)
     gi = np.sort(rng.integers(0, q0 * 4, size=(1, 1, chunks - q0, 12)), axis=-1)
     _check(w, q0, gi, seed=q0)
+
+
+@pytest.mark.parametrize("d,kv,ratio,q_ranges", [
+    (64, 4, 1, False),      # micro-batches: the same queries' chunks, other gradients
+    (64, 4, 1, True),       # query ranges of one sequence
+    (128, 2, 2, True),
+])
+def test_overlapping_backwards_add_into_the_same_gradients(d, kv, ratio, q_ranges):
+    """Calls on several streams that add into one dk and dv lose no sum."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2606_30709_amd import hga
+    nc, n_calls = 96, 4
+    w = W.preset("smalllm").with_(batch=2, n_q_heads=kv * ratio, n_kv_heads=kv, head_dim=d,
+                                  seq_len=64 * nc, topk_groups=12, topk_chunks=8,
+                                  needle_mode="none")
+    plan = hga.Plan.for_workload(w)
+    g = torch.Generator(device="cuda").manual_seed(d + ratio)
+    bf = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    k, v = bf(2, kv, 64 * nc, d), bf(2, kv, 64 * nc, d)
+    calls = []
+    for i in range(n_calls):
+        q0, n = (i * nc // n_calls, nc // n_calls) if q_ranges else (0, nc)
+        q, dout = bf(2, kv * ratio, n * 64, d), bf(2, kv * ratio, n * 64, d)
+        top = torch.arange(q0, q0 + n, device="cuda").view(1, 1, n, 1) * 4
+        ids = (torch.rand(2, kv, n, 12, generator=g, device="cuda") * top).int().sort(-1).values
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device="cuda")
+        hga.hga_gather_attend(plan, q, q0, k, v, ids, None, None, out, lse)
+        calls.append((q, q0, ids, out, lse, dout, torch.empty(q.shape, device="cuda")))
+
+    def add(call, dk, dv, stream=None):
+        q, q0, ids, out, lse, dout, dq = call
+        hga.hga_attend_backward(plan, q, q0, k, v, ids, out, lse, dout, dq, dk, dv, stream=stream)
+
+    want = [torch.zeros(k.shape, dtype=torch.float64, device="cuda") for _ in range(2)]
+    for call in calls:
+        one = [torch.zeros(k.shape, device="cuda") for _ in range(2)]
+        add(call, *one)
+        for s, x in zip(want, one):
+            s += x
+    for _ in range(3):
+        got = [torch.zeros(k.shape, device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+        streams = [torch.cuda.Stream() for _ in calls]
+        for call, s in zip(calls, streams):
+            add(call, *got, stream=s)
+        torch.cuda.synchronize()
+        for x, ref in zip(got, want):
+            assert (x.double() - ref).abs().max() <= 1e-5 * ref.abs().max()
