@@ -7,8 +7,8 @@
 
 namespace hga {
 
-// Key chunks of a (batch, KV head) the inverted lists cover (one LDS counter
-// each while they are built).
+// Key chunks of a (batch, KV head) whose inverted lists one workgroup builds
+// (one LDS counter each).
 constexpr int kBwdIndexChunks = 16384;
 
 // Whether the lists and D_i fit the dq buffer (they do unless a few query

@@ -9,11 +9,12 @@
 // add per 64 products' worth of work, and the L2's atomic rate (about 0.3 T
 // adds/s) sets the pace.  Here the pairs are inverted first:
 //
-//   bwd_index_kernel      one workgroup per (batch, KV head) counts, scans
-//                         and fills, per key chunk, the list of (query unit,
-//                         opened groups) entries, and cuts long lists (sink
-//                         chunks, chunks everybody looks up) into segments;
-//                         the others compute the row statistics.
+//   bwd_index_kernel      one workgroup per (batch, KV head) and 16,384 key
+//                         chunks counts, scans and fills, per key chunk, the
+//                         list of (query unit, opened groups) entries, and
+//                         cuts long lists (sink chunks, chunks everybody looks
+//                         up) into segments; the others compute the row
+//                         statistics.
 //   bwd_chunk_kernel      one workgroup per segment.
 //
 // Where many query heads share a KV head bwd_unit_kernel passes a unit's rows
@@ -42,6 +43,8 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;    // tokens per chunk
 constexpr int kXcds = 8;
+// most 256-thread workgroups of a launch (the runtime takes fewer than 2^32 threads)
+constexpr int64_t kMaxGrid = (int64_t(1) << 24) - kXcds;
 
 // The tables of one (batch, KV head), `stride` ints apart.
 struct Index {
@@ -56,32 +59,38 @@ struct Index {
 };
 
 // The lists and the row statistics in one launch (neither needs the other):
-// the first n_bh workgroups invert one (batch, KV head) each, bound by their
-// two passes over its ids, while the others stream out and dout.
-template <int D>
+// the first workgroups invert one (batch, KV head) each, or a range of its key
+// chunks, bound by their two passes over its ids, while the others stream out
+// and dout.  A workgroup per range: one head x 20,000 chunks of d64 1991 us
+// (whole backward, adding), range after range in one workgroup 2578, unit by
+// unit 4330; x 70,000 chunks 7907, 16636.
+template <int D, bool kWhole>
 __global__ __launch_bounds__(kIndexThreads) void bwd_index_kernel(
     const int32_t* __restrict__ group_idx, int nq, int q_chunk0, int keep_first, int window,
-    int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, Index ix, int n_bh,
+    int topk, int gpc_shift, FastDiv per, int n_chunks, FastDiv ranges, int seg, Index ix, int n_bh,
     int* __restrict__ clear, const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ stat, int64_t rows) {
-    if (blockIdx.x >= n_bh) {
+    const int n_lists = n_bh * ranges.d;
+    if (blockIdx.x >= n_lists) {
         bwd_row_stat<D>(out, dout, lse, stat, rows,
-                        (static_cast<int64_t>(blockIdx.x) - n_bh) * kIndexThreads + threadIdx.x);
+                        (static_cast<int64_t>(blockIdx.x) - n_lists) * kIndexThreads + threadIdx.x);
         return;
     }
-    extern __shared__ int s_cnt[];  // [n_chunks]
+    extern __shared__ int s_cnt[];  // [min(n_chunks, kBwdIndexChunks)]
     __shared__ BwdListsScratch scratch;
-    const int bh = blockIdx.x;
+    const int bh = kWhole ? blockIdx.x : ranges.div(blockIdx.x);
+    const int c0 = kWhole ? 0 : (blockIdx.x - bh * ranges.d) * kBwdIndexChunks;
     struct Workgroup {
         __device__ int thread() const { return threadIdx.x; }
         __device__ void sync() const { __syncthreads(); }
         __device__ int add(int* at, int x) const { return atomicAdd(at, x); }
         __device__ int scan(int x) const { return wave_incl_scan_add(x); }
     };
-    build_bwd_lists(Workgroup{}, group_idx + static_cast<int64_t>(bh) * nq * topk, nq, q_chunk0,
-                    keep_first, window, topk, gpc_shift, per, n_chunks, seg, ix.items(bh),
-                    ix.cap_items, ix.entries(bh),
-                    clear ? clear + static_cast<int64_t>(bh) * n_chunks : nullptr, s_cnt, scratch);
+    build_bwd_lists<kWhole>(
+        Workgroup{}, group_idx + static_cast<int64_t>(bh) * nq * topk, nq, q_chunk0, keep_first,
+        window, topk, gpc_shift, per, n_chunks, c0, min(n_chunks - c0, kBwdIndexChunks), seg,
+        ix.items(bh), ix.cap_items, ix.entries(bh),
+        clear ? clear + static_cast<int64_t>(bh) * n_chunks : nullptr, s_cnt, scratch);
 }
 
 // For a call that writes dk and dv: zeros in the rows of the chunks that the
@@ -308,7 +317,7 @@ void bwd_chunk_kernel(
     if (item.x == 0) return;
     const int chunk = item.x & ((1 << kCountShift) - 1);
     const int r = r_div.d;
-    const int n_ent = (item.x >> kCountShift) & 0x7fff;  // at most 32
+    const int n_ent = (item.x >> kCountShift) & kCountMask;  // at most 32
     const int n_steps = n_ent * r * SPU;
     const bool shared = (item.x >> 30) & 1;
 
@@ -524,8 +533,8 @@ IndexShape index_shape(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
     const int64_t stride = (2 * cap + entries + 3) / 4 * 4;
     const int64_t rows = static_cast<int64_t>(r) * n_q_chunks * KT;  // per (batch, KV head)
     // the row statistics and the tables live in dq
-    s.fits = n_chunks <= kBwdIndexChunks && stride + n_chunks + 2 * rows <= rows * p.head_dim &&
-             cap * p.batch * p.n_kv_heads <= (int64_t(1) << 24) && entries < (int64_t(1) << 30);
+    s.fits = n_chunks <= (1 << kUnitBits) && stride + n_chunks + 2 * rows <= rows * p.head_dim &&
+             cap * p.batch * p.n_kv_heads <= kMaxGrid && entries < (int64_t(1) << 30);
     if (!s.fits) return s;
     s.per = static_cast<int>(per);
     s.n_chunks = static_cast<int>(n_chunks);
@@ -544,10 +553,12 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
     const hga_params& p = plan.p;
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const hipError_t ce = once_per_device(configured, plan.device, [] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_index_kernel<D>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kBwdIndexChunks * 4);
-        if (e != hipSuccess) return e;
+        for (const void* f : {reinterpret_cast<const void*>(&bwd_index_kernel<D, true>),
+                              reinterpret_cast<const void*>(&bwd_index_kernel<D, false>)}) {
+            const hipError_t e = hipFuncSetAttribute(
+                f, hipFuncAttributeMaxDynamicSharedMemorySize, kBwdIndexChunks * 4);
+            if (e != hipSuccess) return e;
+        }
         return hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_chunk_kernel<D, QR, NS>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    ChunkLayout<D, QR, NS>::kBytes);
@@ -560,10 +571,13 @@ hipError_t launch_chunks_t(const hga_plan& plan, const IndexShape& sh, const voi
     const Index ix{reinterpret_cast<int*>(dq + 2 * rows), sh.stride, sh.cap_items};
     int* clear = write ? ix.base + static_cast<int64_t>(n_bh) * sh.stride : nullptr;
     const unsigned stat_blocks = static_cast<unsigned>((rows * 8 + kIndexThreads - 1) / kIndexThreads);
-    hipLaunchKernelGGL((bwd_index_kernel<D>), dim3(n_bh + stat_blocks), dim3(kIndexThreads),
-                       sh.n_chunks * 4, stream, group_idx, n_q_chunks, q_chunk0, p.keep_first,
-                       recent_window(p), p.topk_groups, 6 - group_shift, FastDiv(sh.per),
-                       sh.n_chunks, sh.seg, ix, n_bh, clear, static_cast<const bf16_t*>(out),
+    const int n_ranges = (sh.n_chunks + kBwdIndexChunks - 1) / kBwdIndexChunks;
+    const auto index = n_ranges == 1 ? bwd_index_kernel<D, true> : bwd_index_kernel<D, false>;
+    hipLaunchKernelGGL(index, dim3(n_bh * n_ranges + stat_blocks),
+                       dim3(kIndexThreads), std::min(sh.n_chunks, kBwdIndexChunks) * 4, stream,
+                       group_idx, n_q_chunks, q_chunk0, p.keep_first, recent_window(p),
+                       p.topk_groups, 6 - group_shift, FastDiv(sh.per), sh.n_chunks,
+                       FastDiv(n_ranges), sh.seg, ix, n_bh, clear, static_cast<const bf16_t*>(out),
                        static_cast<const bf16_t*>(dout), lse, dq, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

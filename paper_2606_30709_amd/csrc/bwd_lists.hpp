@@ -16,11 +16,10 @@ constexpr int kIndexThreads = 1024;
 // and whether the chunk is the unit's own (causal mask).
 constexpr int kUnitBits = 22, kMaskShift = 22;
 constexpr uint32_t kCausal = 1u << 30;
-static_assert(kBwdIndexChunks <= 1 << kUnitBits, "unit ids");
-// An item: x = chunk | entries << 15 | (part of a cut list) << 30, y = first
+// An item: x = chunk | entries << 24 | (part of a cut list) << 30, y = first
 // entry.
-constexpr int kCountShift = 15;
-static_assert(kBwdIndexChunks <= 1 << kCountShift, "chunk ids");
+constexpr int kCountShift = 24, kCountMask = 63;
+static_assert(kUnitBits <= kCountShift, "chunk ids (units are chunks too)");
 
 // Calls f(chunk, entry) for every entry of the (batch, KV head), the work
 // spread over the workgroup: slot 0 of unit i is its own chunk, then its
@@ -64,63 +63,86 @@ __host__ __device__ inline void each_entry(const Wg& wg, const int32_t* __restri
 }
 
 struct BwdListsScratch {
-    int sum[2][kIndexThreads / 64];  // per wavefront: entries, segments
-    int segments;                    // all (a word of its own: others still read the sums)
+    // per wavefront: entries and segments of the range, entries before it
+    int sum[3][kIndexThreads / 64];
+    int total[2];  // entries and end of the segments (others still read the sums)
 };
 
-// Counts, scans and fills the lists of one (batch, KV head), kIndexThreads
-// threads.  items: the segments, at most `seg` entries each, then empty ones;
-// clear (or null): per chunk, whether no single segment covers it; cnt:
-// shared, n_chunks.
-template <typename Wg>
+// Counts, scans and fills the lists of the key chunks [c0, c0 + n) of one
+// (batch, KV head), kIndexThreads threads.  A workgroup per range: it looks at
+// all entries, counts those of earlier chunks, and leaves their segments
+// c0 + (their entries) / seg items, which holds them however they are cut.
+// items: the segments, at most `seg` entries each, the unused ones empty up to
+// the next range's first or cap_items; clear (or null): per chunk, whether no
+// single segment covers it; cnt: shared, n counters.  kWhole: the one range is
+// all chunks.
+template <bool kWhole, typename Wg>
 __host__ __device__ inline void build_bwd_lists(
     const Wg& wg, const int32_t* __restrict__ gid, int nq, int q_chunk0, int keep_first, int window,
-    int topk, int gpc_shift, FastDiv per, int n_chunks, int seg, int2* __restrict__ items,
-    int cap_items, uint32_t* __restrict__ entries, int* __restrict__ clear, int* cnt,
-    BwdListsScratch& s) {
+    int topk, int gpc_shift, FastDiv per, int n_chunks, int c0, int n, int seg,
+    int2* __restrict__ items, int cap_items, uint32_t* __restrict__ entries,
+    int* __restrict__ clear, int* cnt, BwdListsScratch& s) {
+    if (kWhole) c0 = 0, n = n_chunks;
     const int tid = wg.thread(), lane = tid & 63, wave = tid >> 6;
-    for (int x = tid; x < n_chunks; x += kIndexThreads) cnt[x] = 0;
+    for (int x = tid; x < n; x += kIndexThreads) cnt[x] = 0;
     wg.sync();
+    int n_before = 0;
     each_entry(wg, gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
-               [&](int chunk, uint32_t) { wg.add(&cnt[chunk], 1); });
+               [&](int chunk, uint32_t) {
+                   if (kWhole || static_cast<uint32_t>(chunk - c0) < static_cast<uint32_t>(n))
+                       wg.add(&cnt[chunk - c0], 1);
+                   else
+                       n_before += chunk < c0;
+               });
     wg.sync();
     // exclusive sums of the entries and of the segments, a run of chunks per thread
-    const int run = (n_chunks + kIndexThreads - 1) / kIndexThreads;
-    const int lo = tid * run < n_chunks ? tid * run : n_chunks;
-    const int hi = lo + run < n_chunks ? lo + run : n_chunks;
+    const int run = (n + kIndexThreads - 1) / kIndexThreads;
+    const int lo = tid * run < n ? tid * run : n;
+    const int hi = lo + run < n ? lo + run : n;
     int n_ent = 0, n_seg = 0;
     for (int x = lo; x < hi; ++x) {
         n_ent += cnt[x];
         n_seg += (cnt[x] + seg - 1) / seg;
     }
     int at_ent = wg.scan(n_ent), at_seg = wg.scan(n_seg);
+    const int before_sum = kWhole ? 0 : wg.scan(n_before);
     if (lane == 63) {
         s.sum[0][wave] = at_ent;
         s.sum[1][wave] = at_seg;
+        s.sum[2][wave] = before_sum;
     }
     wg.sync();
-    at_ent -= n_ent;
-    at_seg -= n_seg;
+    int before = 0;
+    if (!kWhole)
+        for (int w = 0; w < kIndexThreads / 64; ++w) before += s.sum[2][w];
+    at_ent += before - n_ent;
+    at_seg += c0 + before / seg - n_seg;
     for (int w = 0; w < wave; ++w) {
         at_ent += s.sum[0][w];
         at_seg += s.sum[1][w];
     }
     for (int x = lo; x < hi; ++x) {
-        const int n = cnt[x];
+        const int m = cnt[x];
         cnt[x] = at_ent;  // the fill's cursor
-        if (clear) clear[x] = n == 0 || n > seg;
-        for (int o = 0; o < n; o += seg)
+        if (clear) clear[c0 + x] = m == 0 || m > seg;
+        for (int o = 0; o < m; o += seg)
             items[at_seg++] = make_int2(
-                x | (n - o < seg ? n - o : seg) << kCountShift | (n > seg) << 30, at_ent + o);
-        at_ent += n;
+                (c0 + x) | (m - o < seg ? m - o : seg) << kCountShift | (m > seg) << 30, at_ent + o);
+        at_ent += m;
     }
+    if (tid == kIndexThreads - 1) {
+        s.total[0] = at_ent;
+        s.total[1] = at_seg;
+    }
+    wg.sync();
     // the unused items have no entries
-    if (tid == kIndexThreads - 1) s.segments = at_seg;
-    wg.sync();
-    for (int x = s.segments + tid; x < cap_items; x += kIndexThreads) items[x] = make_int2(0, 0);
-    wg.sync();
+    const int end = c0 + n < n_chunks ? c0 + n + s.total[0] / seg : cap_items;
+    for (int x = s.total[1] + tid; x < end; x += kIndexThreads) items[x] = make_int2(0, 0);
     each_entry(wg, gid, nq, q_chunk0, keep_first, window, topk, gpc_shift, per,
-               [&](int chunk, uint32_t e) { entries[wg.add(&cnt[chunk], 1)] = e; });
+               [&](int chunk, uint32_t e) {
+                   if (kWhole || static_cast<uint32_t>(chunk - c0) < static_cast<uint32_t>(n))
+                       entries[wg.add(&cnt[chunk - c0], 1)] = e;
+               });
 }
 
 }  // namespace hga

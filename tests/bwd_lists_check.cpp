@@ -88,7 +88,7 @@ void run(Machine& m, const std::vector<int>& order) {
     } while (0)
 
 bool check(Machine& m, int nq, int q_chunk0, int first, int window, int group, int topk, int seg,
-           int n_bh, const std::vector<int>& order, const char* name) {
+           int range, int n_bh, const std::vector<int>& order, const char* name) {
     const int gpc = 64 / group, n_chunks = q_chunk0 + nq;
     const int gpc_shift = gpc == 8 ? 3 : gpc == 4 ? 2 : 1;
     const int per = 1 + VisibleChunks(n_chunks - 1, first, window).count + topk;
@@ -102,16 +102,20 @@ bool check(Machine& m, int nq, int q_chunk0, int first, int window, int group, i
                 gid[size_t(i) * topk + s] = rng() % 9 == 0 ? -1 : lo + int(rng() % unsigned(c * gpc + 3 - lo));
             }
         const int guard = 64, fill = 0x5a5a5a5a;
-        std::vector<int> clear(n_chunks + guard, fill), cnt(n_chunks + guard, fill);
+        std::vector<int> clear(n_chunks + guard, fill), cnt(std::min(range, n_chunks) + guard, fill);
         std::vector<int2> items(cap + guard, make_int2(fill, fill));
         std::vector<uint32_t> entries(n_ent + guard, fill);
         BwdListsScratch scratch;
+        int c0 = 0;
         m.body = [&] {
-            build_bwd_lists(HostWorkgroup{}, gid.data(), nq, q_chunk0, first, window, topk, gpc_shift,
-                            FastDiv(per), n_chunks, seg, items.data(), cap, entries.data(),
-                            clear.data(), cnt.data(), scratch);
+            const auto build = range < n_chunks ? build_bwd_lists<false, HostWorkgroup>
+                                                : build_bwd_lists<true, HostWorkgroup>;
+            build(HostWorkgroup{}, gid.data(), nq, q_chunk0, first, window, topk, gpc_shift,
+                  FastDiv(per), n_chunks, c0, std::min(range, n_chunks - c0), seg, items.data(), cap,
+                  entries.data(), clear.data(), cnt.data(), scratch);
         };
-        run(m, order);
+        // the ranges' workgroups in descending order: none waits for an earlier one
+        for (c0 = (n_chunks - 1) / range * range; c0 >= 0; c0 -= range) run(m, order);
         // per chunk, how often each unit's groups count, and its causal entries
         using Key = std::pair<int, int>;  // unit, group of the chunk (gpc: causal)
         std::vector<std::map<Key, int>> want(n_chunks), got(n_chunks);
@@ -129,8 +133,9 @@ bool check(Machine& m, int nq, int q_chunk0, int first, int window, int group, i
         std::vector<int> segments(n_chunks), listed(n_chunks);
         std::vector<char> used(n_ent);
         for (int x = 0; x < cap; ++x) {
+            CHECK(items[x].x != fill);
             if (items[x].x == 0) continue;
-            const int chunk = items[x].x & ((1 << kCountShift) - 1), n = (items[x].x >> kCountShift) & 0x7fff;
+            const int chunk = items[x].x & ((1 << kCountShift) - 1), n = (items[x].x >> kCountShift) & kCountMask;
             CHECK(chunk < n_chunks && n >= 1 && n <= seg);
             CHECK(items[x].y >= 0 && items[x].y + n <= n_ent);
             ++segments[chunk];
@@ -155,7 +160,7 @@ bool check(Machine& m, int nq, int q_chunk0, int first, int window, int group, i
             CHECK(clear[x] == (segments[x] != 1));
         }
         for (int x = 0; x < guard; ++x)
-            CHECK(clear[n_chunks + x] == fill && cnt[n_chunks + x] == fill &&
+            CHECK(clear[n_chunks + x] == fill && cnt[cnt.size() - 1 - x] == fill &&
                   items[cap + x].x == fill && entries[n_ent + x] == uint32_t(fill));
     }
     return true;
@@ -174,10 +179,11 @@ int main() {
         const std::vector<int>& order;
     } orders[] = {{"first wavefront first", up}, {"last wavefront first", down}, {"mixed", odd}};
     for (const auto& o : orders) {
-        const bool ok = check(m, 192, 0, 1, 1, 16, 12, 32, 3, o.order, o.name) &&   // three wavefronts with chunks
-                        check(m, 21, 0, 2, 3, 8, 21, 8, 2, o.order, o.name) &&      // one
-                        check(m, 5, 130, 1, 2, 32, 7, 2, 2, o.order, o.name) &&     // few units, long history
-                        check(m, 1100, 300, 1, 1, 16, 4, 4, 1, o.order, o.name);    // two chunks a thread
+        const bool ok = check(m, 192, 0, 1, 1, 16, 12, 32, 16384, 3, o.order, o.name) &&  // three wavefronts with chunks
+                        check(m, 21, 0, 2, 3, 8, 21, 8, 16384, 2, o.order, o.name) &&     // one
+                        check(m, 5, 130, 1, 2, 32, 7, 2, 16384, 2, o.order, o.name) &&    // few units, long history
+                        check(m, 1100, 300, 1, 1, 16, 4, 4, 16384, 1, o.order, o.name) && // two chunks a thread
+                        check(m, 60, 140, 1, 2, 16, 9, 4, 64, 2, o.order, o.name);        // several ranges, the last partly full
         if (!ok) return 1;
         std::printf("%s: right\n", o.name);
     }
