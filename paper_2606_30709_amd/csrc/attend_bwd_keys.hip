@@ -370,6 +370,16 @@ void bwd_chunk_kernel(
                         e & lane_bit ? 0.f : -INFINITY};
     });
 
+    // Whether anybody opened the group of the lane's rows: a wavefront's keys
+    // are one group, or a group in rows 0 .. 7 and another in 8 .. 15.  The
+    // others are not added to (a unit that opened one group of sixteen keys
+    // costs that many rows of atomics, not 64) and are zeros in a call that
+    // writes, whatever their keys hold.
+    const uint32_t row_bit = 1u << (kMaskShift + ((wave * 16 + g4 * 4) >> group_shift));
+    const bool low = __builtin_amdgcn_ballot_w64((elist & (wave_bits & -wave_bits)) != 0) != 0;
+    const bool high = __builtin_amdgcn_ballot_w64((elist & wave_bits & (wave_bits - 1)) != 0) != 0;
+    const bool opened = row_bit & wave_bits & -wave_bits ? low : high;
+
     // In a call that writes, the chunk's only segment writes (nobody else
     // touches its rows in this launch) and the segments of a cut list add to
     // rows that bwd_clear_kernel zeroed.  A call that adds does so atomically
@@ -382,10 +392,10 @@ void bwd_chunk_kernel(
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                __builtin_nontemporal_store(ak[nb][x] * ksc, dk + at0 + x * D + nb * 16);
-                __builtin_nontemporal_store(av[nb][x], dv + at0 + x * D + nb * 16);
+                __builtin_nontemporal_store(opened ? ak[nb][x] * ksc : 0.f, dk + at0 + x * D + nb * 16);
+                __builtin_nontemporal_store(opened ? av[nb][x] : 0.f, dv + at0 + x * D + nb * 16);
             }
-    } else {
+    } else if (opened) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll

@@ -194,3 +194,45 @@ def test_overlapping_backwards_add_into_the_same_gradients(d, kv, ratio, q_range
         torch.cuda.synchronize()
         for x, ref in zip(got, want):
             assert (x.double() - ref).abs().max() <= 1e-5 * ref.abs().max()
+
+
+@pytest.mark.parametrize("d,group,kg", [(64, 8, 5), (64, 16, 3), (64, 32, 2), (128, 8, 4), (128, 16, 5)])
+def test_rows_that_no_query_attends(d, group, kg):
+    """A chunk of which only some groups were opened: the other groups' rows
+    are not added to (minus zeros stay) and are zeros in the writing form,
+    whatever their keys hold."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2606_30709_amd import hga
+    nc, n, kv, gpc = 40, 12, 2, 64 // group
+    w = W.preset("smalllm").with_(batch=1, n_q_heads=kv, n_kv_heads=kv, head_dim=d, seq_len=64 * nc,
+                                  group=group, topk_groups=kg, topk_chunks=kg, needle_mode="none")
+    plan, q0 = hga.Plan.for_workload(w), nc - n
+    g = torch.Generator(device="cuda").manual_seed(d + group)
+    bf = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    q, dout = bf(1, kv, n * 64, d), bf(1, kv, n * 64, d)
+    k, v = bf(1, kv, 64 * nc, d), bf(1, kv, 64 * nc, d)
+    # groups 0, 2, .. of a chunk (0 and 1 of two): never its last
+    ids = torch.randint(2, q0 - 2, (1, kv, n, kg), generator=g, device="cuda") * gpc
+    ids = (ids + torch.randint(0, max(1, gpc // 2), ids.shape, generator=g, device="cuda") * 2).int()
+    ids = ids.sort(-1).values
+    seen = torch.zeros(kv, 64 * nc, dtype=torch.bool, device="cuda")
+    for i in range(n):
+        for c in [q0 + i, *hga.hga_visible_chunks(plan.params, q0 + i)]:
+            seen[:, c * 64:(c + 1) * 64] = True
+    for h in range(kv):
+        for x in ids[0, h].unique().tolist():
+            seen[h, x * group:(x + 1) * group] = True
+    partly = seen.view(kv, nc, 64)
+    assert bool((partly.any(-1) & ~partly.all(-1)).any())
+    k[0][~seen], v[0][~seen] = float("nan"), float("inf")
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device="cuda")
+    hga.hga_gather_attend(plan, q, q0, k, v, ids, None, None, out, lse)
+    dq = torch.empty(q.shape, device="cuda")
+    for fn, before, after in ((hga.hga_attend_backward, -0.0, -2 ** 31), (hga.hga_attend_backward_write, float("nan"), 0)):
+        dk, dv = (torch.full(k.shape, before, device="cuda") for _ in range(2))
+        fn(plan, q, q0, k, v, ids, out, lse, dout, dq, dk, dv)
+        torch.cuda.synchronize()
+        for x in (dk[0], dv[0]):
+            assert bool((x[~seen].view(torch.int32) == after).all())
+            assert bool(x[seen].isfinite().all()) and bool((x[seen] != 0).any())
