@@ -363,15 +363,25 @@ __global__ __launch_bounds__(256) void attend_bwd_begin_kernel(
 //   heads 342 / 232, 4 heads 383 / 356, 6 heads 437 / 527, 8 heads 465 / 604;
 //   4 x 512, K_g 48: 4 heads 2157 / 1869, 8 heads 2796 / 3633; 1 x 50, K_g 12:
 //   2 heads 42 / 50, 4 heads 47 / 71.
-// (One head: equal where launches are small, chunk by chunk from there on.)
+// Every key chunk of the range has a place in the lists, whether anybody
+// attends it or not: 0.2 units of the rule for its counter and its workgroup,
+// which count where few query chunks follow a long history.  One query head,
+// K_g 12, adding: 64 (batch, KV head) pairs x 2 chunks after 3,000 of d128 60 /
+// 123, x 8 190 / 230 (d64 100 / 130), x 32 725 / 659 (d64 376 / 347); 12 pairs x
+// 16 after 4,000 81 / 78 (d64 46 / 50), x 1 after 2,000 23 / 35.  Longer launch
+// (8500): not for one head, where the forms are equal in small launches and
+// the lists ahead from there on.
 bool by_chunk(const hga_plan& plan, int q_chunk0, int n_q_chunks, int fixed, int tiles) {
     const hga_params& p = plan.p;
     const int r = p.n_q_heads / p.n_kv_heads;
-    const double units = static_cast<double>(p.batch) * p.n_kv_heads * n_q_chunks;
+    const double pairs = static_cast<double>(p.batch) * p.n_kv_heads;
+    const double units = pairs * n_q_chunks;
     const double entries = units * (fixed + std::min(p.topk_chunks, p.topk_groups));
     const double by_unit = units * tiles * ((p.head_dim == 64 ? 8 : 13) + r);
-    const double chunks = entries * r * (p.head_dim == 64 ? 1.13 : 1.75) + 8500;
-    return (r == 1 || chunks <= by_unit) && bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
+    const double chunks = entries * r * (p.head_dim == 64 ? 1.13 : 1.75) +
+                          pairs * (static_cast<double>(q_chunk0) + n_q_chunks) * 0.2 +
+                          (r == 1 ? 0 : 8500);
+    return chunks <= by_unit && bwd_chunks_fit(plan, q_chunk0, n_q_chunks);
 }
 
 template <int D, int KS, int NW>

@@ -132,9 +132,12 @@ def test_backward_lists_of_several_heads(d, group, ratio, kg, first, last):
 
 @pytest.mark.parametrize("d,chunks,q0", [
     (64, 2050, 2049),    # the lists do not fit one query chunk's dq
-    (64, 2050, 2042),    # they fit eight's
-    (64, 16410, 16370),  # key chunks in two ranges
+    (64, 2050, 2042),    # they fit eight's, unit by unit is the faster
+    (64, 2050, 2026),    # chunk by chunk
+    (64, 16410, 16370),
+    (64, 16400, 16240),  # key chunks in two ranges
     (128, 70, 69),
+    (128, 70, 66),
 ])
 def test_backward_few_query_chunks_after_a_long_history(d, chunks, q0):
     if not torch.cuda.is_available():
