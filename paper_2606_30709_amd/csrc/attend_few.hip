@@ -466,12 +466,33 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
 
 }  // namespace
 
-// One workgroup per CU: launches that fit the chip once.
-bool attend_few_applies(const hga_plan& plan, int n_q_chunks) {
+// Where this form is the faster one: launches whose query tiles fit the chip
+// once, up to a number of key tiles.  One CU takes all keys of a query tile, at
+// 0.22 us a tile of d64 and 0.46 of d128, while the split form spreads them
+// (0.05 to 0.25) but pays a second launch and the partial results' way, the
+// more the more query tiles there are.  hga_attend_split, here / split form, us,
+// by query tiles and key tiles:
+//   d64   4: 10 8.1/8.0, 28 12.7/8.9, 260 63/23;  64: 16 9.1/10.1, 28 13.2/11.9;
+//         128: 28 13.6/14.4, 52 21.5/17.4;  256 (4 splits): 16 12.3/14.7, 28 18.8/17.6
+//   d128  4: 10 11.1/11.1, 28 21.9/12.0, 260 132/30;  64: 16 13.0/17.6, 28 22.9/21.4;
+//         128: 28 23.9/25.7, 52 38.5/28.0;  256 (8 splits): 28 24.1/26.7, 52 38/32;
+//         256 (4 splits): 10 16.1/21.3, 16 23.2/20.2
+// Few splits are few wavefronts, each with a long run of tiles: two splits of
+// 64 query tiles, 10 key tiles 13.1/11.1 (d64) and 17.9/19.0, 16 18.9/14.0 and
+// 25.8/23.9; four splits, 16 11.3/10.8 and 15.7/18.6, 28 17.2/13.7 and 24.1/23.4.
+bool attend_few_fits(const hga_plan& plan, int n_q_chunks) {
     const hga_params& p = plan.p;
     const int64_t tiles = 2 * static_cast<int64_t>(p.batch) * p.n_q_heads * n_q_chunks;
     const int lds = p.head_dim == 64 ? FewLayout<64>::bytes(16) : FewLayout<128>::bytes(10);
     return tiles <= plan.n_cu && lds <= plan.max_lds;
+}
+
+bool attend_few_applies(const hga_plan& plan, int n_q_chunks, int n_tiles, int n_split) {
+    const hga_params& p = plan.p;
+    if (!attend_few_fits(plan, n_q_chunks)) return false;
+    const int q_tiles = 2 * p.batch * p.n_q_heads * n_q_chunks;
+    return n_tiles <= 10 + q_tiles * 51 / plan.n_cu &&
+           n_tiles <= (p.head_dim == 64 || 2 * q_tiles <= plan.n_cu || n_split >= 8 ? 4 : 3) * n_split;
 }
 
 hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,

@@ -1019,14 +1019,18 @@ static int most_splits(const hga_plan& plan, int n_q_chunks, int64_t workspace_b
     return static_cast<int>(want < fit ? want : fit);
 }
 
+// Key tiles of a unit: of the last query chunk, which sees the most chunks.
+static int key_tiles(const hga_plan& plan, int q_chunk0, int n_q_chunks) {
+    const hga_params& p = plan.p;
+    return 1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, recent_window(p)).count +
+           (p.topk_groups * p.group + KT - 1) / KT;
+}
+
 // Splits for a launch of n_q_chunks query chunks from q_chunk0: the most, with
 // at least two key tiles per split.
 int attend_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks, int64_t workspace_bytes) {
-    const hga_params& p = plan.p;
     const int most = most_splits(plan, n_q_chunks, workspace_bytes);
-    const int n_rt = (p.topk_groups * p.group + KT - 1) / KT;
-    const int n_tiles =
-        1 + VisibleChunks(q_chunk0 + n_q_chunks - 1, p.keep_first, recent_window(p)).count + n_rt;
+    const int n_tiles = key_tiles(plan, q_chunk0, n_q_chunks);
     return most < (n_tiles + 1) / 2 ? most : (n_tiles + 1) / 2;
 }
 
@@ -1041,7 +1045,7 @@ hipError_t launch_attend_split(const hga_plan& plan, const void* q_rot, int q_ch
         return launch_attend(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                              res_slot, k_routed, v_routed, group_idx, out, lse, nullptr, nullptr,
                              stream);
-    if (attend_few_applies(plan, n_q_chunks))
+    if (attend_few_applies(plan, n_q_chunks, key_tiles(plan, q_chunk0, n_q_chunks), n_split))
         return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                  res_slot, const_cast<void*>(k_routed),
                                  const_cast<void*>(v_routed), group_idx, out, lse, n_split, stream,
@@ -1081,7 +1085,9 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
     // the host link they pass once instead: gathered to the routed buffers, or
     // to the workspace when there are none and it is large enough (else by the
     // splits, which copy each row once a unit).
-    if (attend_few_applies(plan, n_q_chunks)) {
+    const bool few = attend_few_applies(plan, n_q_chunks, key_tiles(plan, q_chunk0, n_q_chunks),
+                                        n_split);
+    if (few || (src_on_host && attend_few_fits(plan, n_q_chunks))) {
         if (!src_on_host)
             return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                      res_slot, k_routed, v_routed, group_idx, out, lse, n_split,

@@ -155,7 +155,9 @@ int attend_splits(const hga_plan& plan, int q_chunk0, int n_q_chunks, int64_t wo
 // k_routed / v_routed, or (k_src given) gathered from k_src / v_src and written
 // to k_routed / v_routed when those are given.  block_major: every query chunk
 // stands for a call of its own, with at most n_split splits.
-bool attend_few_applies(const hga_plan& plan, int n_q_chunks);
+// _fits: may be taken; _applies: and is the faster one, for n_tiles key tiles.
+bool attend_few_fits(const hga_plan& plan, int n_q_chunks);
+bool attend_few_applies(const hga_plan& plan, int n_q_chunks, int n_tiles, int n_split);
 hipError_t launch_attend_few(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                              const void* k_res, const void* v_res, int64_t res_tokens,
                              const int32_t* res_slot, void* k_routed, void* v_routed,

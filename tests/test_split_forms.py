@@ -9,7 +9,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import hga_oracle as O
 from paper_2606_30709_amd import workloads as W
+
+from parity_util import LSE_TOL, OUT_TOL, tensor_to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -26,7 +29,7 @@ class _Case:
     """Random inputs of `n` query chunks after `q0`, with ids of the causal
     past, some padded, repeated or in the future."""
 
-    def __init__(self, d, kv, ratio, group, kg, first, last, q0, n, batch=1, seed=0):
+    def __init__(self, d, kv, ratio, group, kg, first, last, q0, n, batch=1, seed=0, distinct=False):
         if not torch.cuda.is_available():
             pytest.skip("needs a GPU")
         from paper_2606_30709_amd import hga
@@ -46,7 +49,9 @@ class _Case:
         for i in range(n):
             c = q0 + i
             if c:
-                gi[:, :, i] = np.sort(rng.integers(0, c * gpc, size=(batch, kv, kg)), axis=-1)
+                draw = ((lambda: rng.choice(c * gpc, kg, replace=False)) if distinct else
+                        (lambda: rng.integers(0, c * gpc, size=kg)))
+                gi[:, :, i] = [[np.sort(draw()) for _ in range(kv)] for _ in range(batch)]
                 if i % 3 == 1:
                     gi[:, :, i, kg // 2:] = -1
                 if i % 4 == 2:
@@ -99,6 +104,47 @@ def test_few_units_form_has_the_split_forms_bits(d, kv, ratio, group, kg, first,
         o1, l1 = t.attend_split(i, 1, t.hga.hga_attend_split_workspace(t.plan, 1))
         s = slice(i * 64, (i + 1) * 64)
         assert _same(o1, out[:, :, s]) and _same(l1, lse[:, :, s]), i
+
+
+@pytest.mark.parametrize("d,kv,ratio,group,kg,first,last,q0,n,batch", [
+    # more query tiles than compute units: the merge kernel
+    (128, 4, 8, 16, 48, 1, 2, 13, 5, 1),
+    (128, 2, 3, 32, 11, 2, 1, 7, 16, 2),
+    (64, 3, 3, 8, 30, 1, 1, 7, 16, 1),
+    (64, 1, 9, 16, 25, 0, 3, 8, 8, 2),
+    # few query tiles and many key tiles: the merge kernel too
+    (128, 1, 2, 32, 120, 1, 1, 70, 1, 1),
+    (64, 2, 4, 16, 140, 2, 1, 40, 2, 1),
+    # the last number of key tiles of the one-workgroup form for four query
+    # tiles (10), and the first past it
+    (128, 1, 2, 16, 25, 1, 1, 12, 1, 1),
+    (128, 1, 2, 16, 29, 1, 1, 12, 1, 1),
+    (64, 1, 2, 8, 50, 1, 1, 12, 1, 1),
+    (64, 1, 2, 8, 57, 1, 1, 12, 1, 1),
+])
+def test_split_forms_match_oracle(d, kv, ratio, group, kg, first, last, q0, n, batch):
+    """Routed rows from buffers, and gathered with and without buffers, against
+    the float64 oracle; the three are the same bits."""
+    t = _Case(d, kv, ratio, group, kg, first, last, q0, n, batch, seed=kg, distinct=True)
+    hga, w = t.hga, t.w
+    nbytes = hga.hga_attend_split_workspace(t.plan, n)
+    out, lse = t.attend_split(0, n, nbytes)
+    gi = t.gi.cpu().numpy()
+    lim = (np.arange(q0, q0 + n) * (64 // group))[None, None, :, None]
+    ref = O.attend(*(tensor_to_f64(x) for x in (t.q, t.k, t.v)), np.where(gi < lim, gi, -1),
+                   list(range(q0, q0 + n)), 64, group, first, last, w.force_prev)
+    assert np.abs(tensor_to_f64(out) - ref[0]).max() <= OUT_TOL["bf16"]
+    assert np.abs(tensor_to_f64(lse) - ref[1]).max() <= LSE_TOL["bf16"]
+    for buffers in (False, True):
+        kr, vr = torch.full_like(t.kr, float("nan")), torch.full_like(t.vr, float("nan"))
+        o2, l2 = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+        ws = torch.full((nbytes // 4,), float("nan"), device="cuda")
+        hga.hga_gather_attend_split(t.plan, t.q, q0, t.k, t.v, t.k, t.v, t.gi, kr if buffers else None,
+                                    vr if buffers else None, o2, ws, l2)
+        torch.cuda.synchronize()
+        assert _same(o2, out) and _same(l2, lse), buffers
+        if buffers:
+            assert _same(kr, t.kr) and _same(vr, t.vr)
 
 
 @pytest.mark.parametrize("d,ratio,group,kg,splits", [
