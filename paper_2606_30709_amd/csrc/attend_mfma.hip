@@ -1081,32 +1081,53 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
         return launch_mfma_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
                                      res_slot, k_routed, v_routed, group_idx, out, lse, nullptr,
                                      nullptr, stream, k_src, v_src, src_tokens);
-    // Few units: every query tile's workgroup copies the routed rows.  Over
-    // the host link they pass once instead: gathered to the routed buffers, or
-    // to the workspace when there are none and it is large enough (else by the
-    // splits, which copy each row once a unit).
     const bool few = attend_few_applies(plan, n_q_chunks, key_tiles(plan, q_chunk0, n_q_chunks),
                                         n_split);
-    if (few || (src_on_host && attend_few_fits(plan, n_q_chunks))) {
-        if (!src_on_host)
-            return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                                     res_slot, k_routed, v_routed, group_idx, out, lse, n_split,
-                                     stream, k_src, v_src, src_tokens);
+    if (few && !src_on_host)
+        return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
+                                 res_slot, k_routed, v_routed, group_idx, out, lse, n_split, stream,
+                                 k_src, v_src, src_tokens);
+    // Over the host link a row costs more than anything done with it.  Where
+    // one workgroup takes all query tiles of a unit the split form copies each
+    // row once, while its other workgroups compute (2/1 heads x 96 routed
+    // tiles of d64 40 us, gathered first and then by query tile 63; d128 72 and
+    // 120).  With more workgroups a unit each copies it (32/4 heads of d128, 24
+    // routed tiles 153 us, 96 500; gathered first 83 and 265), so the rows are
+    // gathered ahead of the attention: to the routed buffers, or to the
+    // workspace behind the partial results, or, with room for the rows alone, in
+    // their place and by query tile.  d128 gains by that with one workgroup too
+    // where query tiles are many and key tiles few (16/8 heads x 4 chunks, 6
+    // routed tiles 131 us, not 149; 4 query tiles 22, not 17).
+    if (src_on_host && attend_few_fits(plan, n_q_chunks)) {
+        const int r = p.n_q_heads / p.n_kv_heads;
+        const bool one_workgroup = 2 * r <= (p.head_dim == 128 ? kD128Waves : 4);
+        const bool many_tiles = 2 * p.batch * p.n_q_heads * n_q_chunks >= plan.n_cu / 8;
+        const bool ahead = !one_workgroup || (few && p.head_dim == 128 && many_tiles);
         const int64_t bytes = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks *
                               p.topk_groups * p.group * p.head_dim * 2;
+        const int64_t partials = n_split * attend_split_bytes_per_split(plan, n_q_chunks);
+        bool by_tile = few;
         void* kr = k_routed;
         void* vr = v_routed;
-        if (!kr && 2 * bytes <= workspace_bytes) {
-            kr = workspace;
-            vr = static_cast<unsigned char*>(workspace) + bytes;
+        if (ahead && !kr) {
+            if (!by_tile && partials + 2 * bytes > workspace_bytes) by_tile = true;
+            const int64_t at = by_tile ? 0 : partials;
+            if (at + 2 * bytes <= workspace_bytes) {
+                kr = static_cast<unsigned char*>(workspace) + at;
+                vr = static_cast<unsigned char*>(kr) + bytes;
+            }
         }
-        if (kr) {
+        if (ahead && kr) {
             const hipError_t e = launch_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_src,
                                                   v_src, src_tokens, kr, vr, stream);
             if (e != hipSuccess) return e;
-            return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
-                                     res_slot, kr, vr, group_idx, out, lse, n_split, stream, nullptr,
-                                     nullptr, 0);
+            if (by_tile)
+                return launch_attend_few(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,
+                                         res_tokens, res_slot, kr, vr, group_idx, out, lse,
+                                         n_split, stream, nullptr, nullptr, 0);
+            return launch_split_any<false>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res,
+                                           res_tokens, res_slot, kr, vr, group_idx, out, lse,
+                                           static_cast<float*>(workspace), n_split, stream);
         }
     }
     return launch_split_any<true>(plan, q_rot, q_chunk0, n_q_chunks, k_res, v_res, res_tokens,
@@ -1114,7 +1135,6 @@ hipError_t launch_gather_attend_split(const hga_plan& plan, const void* q_rot, i
                                   static_cast<float*>(workspace), n_split, stream, k_src, v_src,
                                   src_tokens);
 }
-
 
 hipError_t launch_attend(const hga_plan& plan, const void* q_rot, int q_chunk0, int n_q_chunks,
                          const void* k_res, const void* v_res, int64_t res_tokens,

@@ -184,6 +184,42 @@ def test_host_source_bits_without_room_for_the_routed_rows(d, ratio, group, kg, 
                 assert _same(kr, t.kr[:, :, i:i + n]) and _same(vr, t.vr[:, :, i:i + n])
 
 
+@pytest.mark.parametrize("d,kv,ratio,kg,q0,n", [
+    (128, 2, 2, 16, 20, 1),     # one workgroup a unit, few query tiles: gathered by the splits
+    (128, 8, 2, 16, 20, 4),     # more of them: gathered ahead
+    (128, 4, 8, 24, 20, 1),     # two workgroups a unit: ahead, then by query tile
+    (128, 4, 8, 120, 40, 1),    # ... or, many key tiles, by the splits
+    (64, 4, 2, 16, 20, 1),
+    (64, 2, 5, 12, 20, 2),
+    (64, 2, 5, 120, 40, 1),
+])
+def test_host_source_forms(d, kv, ratio, kg, q0, n):
+    """From host memory: the bits of the two calls that it stands for, with
+    buffers and without, whatever the workspace holds (everything; the rows
+    behind the partial results, exactly; the rows and no more; not the rows)."""
+    t = _Case(d, kv, ratio, 16, kg, 1, 1, q0, n, seed=kg + d)
+    hga = t.hga
+    kh, vh = t.k.cpu().pin_memory(), t.v.cpu().pin_memory()
+    rows = 2 * t.kr.numel() * 2
+    most = hga.hga_attend_split_workspace(t.plan, n)
+    for nbytes in sorted({most, most + rows, rows, rows - 16, 3 * t.split_bytes(n) + rows,
+                          3 * t.split_bytes(n) + rows - 16, 2 * t.split_bytes(n)}):
+        want = t.attend_split(0, n, nbytes)
+        for buffers in (False, True):
+            kr, vr = torch.full_like(t.kr, float("nan")), torch.full_like(t.vr, float("nan"))
+            out, lse = torch.full_like(want[0], float("nan")), torch.full_like(want[1], float("nan"))
+            # (a guard behind the workspace)
+            ws = torch.full((nbytes // 4 + 1024,), 7.0, device="cuda")
+            hga.hga_gather_attend_split(t.plan, t.q, q0, t.k, t.v, kh, vh, t.gi,
+                                        kr if buffers else None, vr if buffers else None, out,
+                                        ws[:nbytes // 4], lse, src_on_host=True)
+            torch.cuda.synchronize()
+            assert _same(out, want[0]) and _same(lse, want[1]), (nbytes, buffers)
+            assert bool((ws[nbytes // 4:] == 7).all())
+            if buffers:
+                assert _same(kr, t.kr) and _same(vr, t.vr)
+
+
 @pytest.mark.parametrize("key,kw,splits", [
     # one tile of routed rows: block 0 has one split, the others two or three
     ("qwen32k", dict(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=64 * 12, topk_groups=4,
