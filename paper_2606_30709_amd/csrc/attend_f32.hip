@@ -96,7 +96,9 @@ void attend_f32_kernel(
     // consecutive items (the query tiles of one unit, then the next unit) on
     // one XCD, whose L2 then holds the unit's keys
     const int per_xcd = (n_items + kXcds - 1) / kXcds;
-    const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int64_t block = linear_block();
+    if (block >= static_cast<int64_t>(per_xcd) * kXcds) return;
+    const int item = static_cast<int>(block % kXcds) * per_xcd + static_cast<int>(block / kXcds);
     if (item >= n_items) return;
     const int unit_id = tile_div.div(item);
     const int qtile = item - unit_id * tile_div.d;
@@ -361,10 +363,10 @@ hipError_t launch_f32_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     if (ce != hipSuccess) return ce;
     const int r = p.n_q_heads / p.n_kv_heads;
     const int64_t items = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * 2 * r;
-    if (items > (int64_t(1) << 23)) return hipErrorInvalidConfiguration;
-    const int grid = static_cast<int>((items + kXcds - 1) / kXcds * kXcds);
+    if (items > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
+    const dim3 grid = grid_of((items + kXcds - 1) / kXcds * kXcds, NW * 64);
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
-    hipExtLaunchKernelGGL((attend_f32_kernel<D>), dim3(grid), dim3(NW * 64), F32Layout<D>::kBytes,
+    hipExtLaunchKernelGGL((attend_f32_kernel<D>), grid, dim3(NW * 64), F32Layout<D>::kBytes,
                           stream, ev_start, ev_stop, 0, static_cast<const float*>(q_rot), q_chunk0,
                           n_q_chunks, static_cast<const float*>(k_res),
                           static_cast<const float*>(v_res), res_tokens, res_slot,

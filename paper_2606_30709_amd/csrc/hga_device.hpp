@@ -70,6 +70,19 @@ struct FastDiv {
     }
 };
 
+// A grid of at least n workgroups of `threads`, its linear_block() numbers
+// 0 .. n - 1 and (kernels return there) some beyond: one dimension while the
+// runtime takes it (fewer than 2^32 threads along x), else rows of a multiple
+// of eight, so that a workgroup's XCD is its number modulo eight.
+inline dim3 grid_of(int64_t n, int threads) {
+    const int64_t most = ((int64_t(1) << 32) - 1) / threads / 8 * 8;
+    if (n <= most) return dim3(static_cast<unsigned>(n));
+    return dim3(static_cast<unsigned>(most), static_cast<unsigned>((n + most - 1) / most));
+}
+__device__ __forceinline__ int64_t linear_block() {
+    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
 // Where query chunk i of head (or (batch, KV head)) h lies among the chunks of
 // a tensor: [head][chunk] of an ordinary call, [chunk][head] of a block-major
 // one.
