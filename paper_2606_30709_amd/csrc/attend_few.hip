@@ -84,7 +84,7 @@ void attend_few_kernel(
     bf16_t* __restrict__ out, float* __restrict__ lse, int r, FastDiv kv_div, FastDiv chunk_div,
     FastDiv tile_div, int group_shift, int keep_first, int window, int topk_groups,
     const bf16_t* __restrict__ k_src, const bf16_t* __restrict__ v_src, int64_t src_tokens,
-    ChunkMap q_map, ChunkMap unit_map, int n_split, int per_unit) {
+    ChunkMap q_map, ChunkMap unit_map, int n_split, int per_unit, int n_blocks) {
     using Lay = FewLayout<D>;
     constexpr int kRow = Lay::kRow;
     constexpr int CPR = D / 8;             // 16-byte chunks per row
@@ -93,8 +93,10 @@ void attend_few_kernel(
     constexpr int NKS = D / 16, NDT = D / 32;
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int item = tile_div.div(blockIdx.x);
-    const int qtile = blockIdx.x - item * tile_div.d;
+    const int64_t block = linear_block();
+    if (block >= n_blocks) return;
+    const int item = tile_div.div(static_cast<uint32_t>(block));
+    const int qtile = static_cast<int>(block) - item * tile_div.d;
     const int bh = chunk_div.div(item);
     const int i = item - bh * n_q_chunks;
     const int64_t unit = unit_map.at(bh, i);
@@ -448,8 +450,10 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     const int r = p.n_q_heads / p.n_kv_heads;
     const int group_shift = p.group == 8 ? 3 : (p.group == 16 ? 4 : 5);
     const int waves = n_split < NW ? n_split : NW;
-    hipLaunchKernelGGL((attend_few_kernel<D, NW, NP, kGather>),
-                       dim3(p.batch * p.n_kv_heads * n_q_chunks * 2 * r), dim3(waves * 64),
+    const int64_t blocks = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * 2 * r;
+    if (blocks > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((attend_few_kernel<D, NW, NP, kGather>), grid_of(blocks, waves * 64),
+                       dim3(waves * 64),
                        FewLayout<D>::bytes(waves), stream, static_cast<const bf16_t*>(q_rot),
                        q_chunk0, n_q_chunks, static_cast<const bf16_t*>(k_res),
                        static_cast<const bf16_t*>(v_res), res_tokens, res_slot,
@@ -460,7 +464,7 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
                        static_cast<const bf16_t*>(v_src), src_tokens,
                        chunk_map(p.batch * p.n_q_heads, n_q_chunks, block_major),
                        chunk_map(p.batch * p.n_kv_heads, n_q_chunks, block_major), n_split,
-                       block_major);
+                       block_major, static_cast<int>(blocks));
     return hipGetLastError();
 }
 
