@@ -51,16 +51,6 @@ __device__ __forceinline__ void wave_mean_rows(int rows, RowVec row_vec, float* 
     }
 }
 
-// Address of token t of query head h of KV head j's group, query chunk i, in
-// the [B, H, n_q_chunks * 64, D] rotated-query layout.
-template <typename T, int D>
-__device__ __forceinline__ const T* query_chunk_base(const T* q_rot, int b, int j, int i,
-                                                     int n_q_heads, int r, int n_q_chunks) {
-    const int64_t qtok = static_cast<int64_t>(n_q_chunks) * 64;
-    return q_rot + ((static_cast<int64_t>(b) * n_q_heads + j * r) * qtok +
-                    static_cast<int64_t>(i) * 64) * D;
-}
-
 // q_bar of query chunk i of the r query heads from head0 on, rows read from HBM.
 template <typename T, int D>
 __device__ __forceinline__ void wave_query_mean(const T* __restrict__ q_rot, int head0, int i, int r,

@@ -721,7 +721,7 @@ __global__ __launch_bounds__(1024) void route_spread_kernel(
     const float* __restrict__ chunk_sum, const float* __restrict__ group_sum, int table_chunks,
     int32_t* __restrict__ chunk_idx, int32_t* __restrict__ group_idx,
     uint64_t* __restrict__ ws_keys, unsigned* __restrict__ ws_count, int n_kv, int keep_first,
-    int window, int topk, int topk_groups, int gpc_shift, int parts, int big_off, int block_bh) {
+    int window, int topk, int topk_groups, int gpc_shift, int parts, int big_off) {
     constexpr int kThreads = 1024;
     constexpr int F4 = D / 4;                        // float4 per table row
     constexpr int TS = D + 4;                        // padded LDS row stride (floats)
@@ -732,8 +732,7 @@ __global__ __launch_bounds__(1024) void route_spread_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int unit = blockIdx.x / parts, part = blockIdx.x % parts;
-    const int bh = block_bh ? unit % block_bh : unit / n_q_chunks;
-    const int i = block_bh ? unit / block_bh : unit % n_q_chunks;
+    const int bh = unit / n_q_chunks, i = unit % n_q_chunks;
     const int c = q_chunk0 + i;
     WaveLds L = carve(smem_raw, D, kGroups ? topk : 0,
                       kGroups && topk_groups > topk ? topk_groups : topk);
@@ -1086,8 +1085,9 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
     const int gpc = p.chunk / p.group;
     const int gpc_shift = gpc == 8 ? 3 : (gpc == 4 ? 2 : 1);
     // a few units with long tables: the scan spread over several workgroups
-    // per unit (q_bar given; the keys in the plan's workspace)
-    if (kQbarIn && units <= kRouteSpreadUnits && n_max >= 2 * kSpreadRows &&
+    // per unit (q_bar given; the keys in the plan's workspace; a block-major
+    // call, all blocks from the first on, has more units than that)
+    if (kQbarIn && !block_bh && units <= kRouteSpreadUnits && n_max >= 2 * kSpreadRows &&
         n_max <= kRouteSpreadCandidates && plan.route_keys) {
         const WideGeom wg = route_wide_geom(plan, n_max, kGroups, true);
         const size_t tab = sizeof(float) * kSpreadRows * (D + 4);
@@ -1099,7 +1099,7 @@ hipError_t launch_route_t(const hga_plan& plan, const void* q_rot, int q_chunk0,
                                table_chunks, chunk_idx, group_idx, plan.route_keys,
                                plan.route_count, p.n_kv_heads, p.keep_first, recent_window(p),
                                p.topk_chunks, p.topk_groups, gpc_shift, parts,
-                               static_cast<int>(wg.big_off), block_bh);
+                               static_cast<int>(wg.big_off));
             return hipGetLastError();
         }
     }

@@ -241,6 +241,9 @@ def test_host_source_forms(d, kv, ratio, kg, q0, n):
     ("smalllm", dict(batch=1, n_q_heads=4, n_kv_heads=2, seq_len=64 * 9), 0),
     ("smalllm", dict(batch=2, n_q_heads=2, n_kv_heads=2, seq_len=64 * 9), 16),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2), 16),
+    # more middle chunks than the resident-key routing holds
+    ("smalllm", dict(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=64 * 1061), 0),
+    ("qwen32k", dict(n_q_heads=2, n_kv_heads=1, seq_len=64 * 1061, topk_groups=9), 4),
 ])
 def test_prefill_blocks_has_block_steps_bits(key, kw, splits):
     """hga_prefill_blocks writes what hga_block_step writes for each block in
