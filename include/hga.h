@@ -333,11 +333,14 @@ hga_status hga_gather_kv_cached(const hga_plan* plan, const int32_t* group_idx, 
 
 /* hga_attend for launches with few units (a decode block, one block of a
  * block-sequential prefill), Sec. 3.4: each unit's key tiles (current chunk,
- * visible chunks, routed rows) are divided among up to 16 workgroups, each
- * of which leaves an unnormalised partial result (fp32 output sums, running
- * maximum and weight sum per query row) in `workspace`; a second kernel
- * merges them with the usual softmax rescaling.  The number of splits is
- * chosen from the unit count, the tile count and what the workspace holds.
+ * visible chunks, routed rows) are divided into up to 16 splits, each with an
+ * unnormalised partial result (fp32 output sums, running maximum and weight
+ * sum per query row) that are merged with the usual softmax rescaling.  The
+ * number of splits is chosen from the unit count, the tile count and what the
+ * workspace holds.  Either every split has workgroups of its own, which leave
+ * the partial results in `workspace` for a second kernel, or (few query and
+ * key tiles) one workgroup takes all splits of 32 query rows and merges them
+ * on chip; the same bits, and which it is depends on sizes alone.
  * out and lse equal hga_attend's up to fp32 summation order (the softmax is
  * the same; its sums are formed in a different order); with one split
  * (workspace_bytes below two splits' worth, the fp32 plan dtype, or one
@@ -404,14 +407,15 @@ int64_t hga_static_scratch_bytes(void);
  *               ((q_chunk0 + n_q_chunks) * chunk <= res_tokens)
  *   group_idx   as for hga_attend
  *   lse         fp32 [batch, n_q_heads, n_q_chunks*chunk] (required)
- *   dq          fp32 like q_rot, written (with GQA groups beyond one
- *               workgroup's query rows the call first keeps D_i in dq's
- *               leading floats, then overwrites all of dq); must not
- *               overlap any other argument
+ *   dq          fp32 like q_rot, written (the call first keeps its row
+ *               statistics and lists there, then overwrites all of dq); must
+ *               not overlap any other argument
  *   dk, dv      fp32 [batch, n_kv_heads, res_tokens, head_dim], ADDED INTO
  *               (zero them for a plain gradient; the sums over query units
  *               are fp32 atomic adds, so their order, and the last bits, may
- *               vary from call to call)
+ *               vary from call to call; calls on several streams may add into
+ *               the same dk and dv at once); rows that no query chunk of the
+ *               call attends are not touched
  * HGA_EUNSUPPORTED for an fp32 plan; other errors as hga_attend. */
 hga_status hga_attend_backward(const hga_plan* plan, const void* q_rot, int32_t q_chunk0,
                                int32_t n_q_chunks, const void* k_res, const void* v_res,
@@ -433,13 +437,16 @@ hga_status hga_attend_backward_write(const hga_plan* plan, const void* q_rot, in
                                      float* dq, float* dk, float* dv, void* stream);
 
 /* hga_gather_kv followed by hga_attend_split, as one pass, for any layout
- * (Sec. 4.3 gather, Sec. 3.4 attention): the workgroups of a unit's routed
- * tiles copy the routed groups' rows straight from k_src/v_src (rows
+ * (Sec. 4.3 gather, Sec. 3.4 attention): the attention's workgroups copy the
+ * routed groups' rows straight from k_src/v_src (rows
  * g*group .. g*group+group-1 of group g, zeros for a padded or future id)
- * while those of its visible tiles already compute, and the staged rows are
+ * while those of visible tiles already compute, and the staged rows are
  * written to k_routed/v_routed.  With the history in pinned host memory
- * (src_on_host = 1: a decode block) the copies over the host link overlap
- * the attention of the resident chunks instead of preceding it.
+ * (src_on_host = 1: a decode block) that is kept to calls in which a row then
+ * crosses the host link once; with more query heads per KV head than one
+ * workgroup takes, a call of few units gathers the rows ahead of the
+ * attention, to k_routed/v_routed or, without those, to the workspace if it
+ * has room.
  * k_routed, v_routed, out and lse receive exactly what
  *   hga_gather_kv(plan, group_idx, q_chunk0, n_q_chunks, k_src, v_src,
  *                 src_tokens, src_on_host, k_routed, v_routed, stream);
@@ -542,10 +549,12 @@ hga_status hga_block_step(const hga_plan* plan, const void* q_block, int32_t c,
  *   k_routed, v_routed  [n_blocks][batch, n_kv_heads, 1, topk_groups*group, head_dim]
  * k_res/v_res hold the whole prompt's keys and values (token-indexed,
  * res_tokens >= n_blocks * chunk); the summary tables are built as the
- * blocks close.  Every block's outputs equal what the bulk prefill
+ * blocks close.  Without a workspace (or with one below two splits of a
+ * block) every block's outputs are those of the bulk prefill
  * (hga_build_summaries, then hga_route and hga_gather_attend over all chunks)
- * writes for the same query chunk.  Arguments are checked before the first
- * launch.  workspace / workspace_bytes as for hga_block_step. */
+ * for the same query chunk, bit for bit; with one, those of hga_block_step with
+ * that workspace, whose splits its size determines (it is not written).
+ * Arguments are checked before the first launch. */
 hga_status hga_prefill_blocks(const hga_plan* plan, const void* q_blocks, int32_t n_blocks,
                               const void* k_res, const void* v_res, int64_t res_tokens,
                               float* chunk_sum, float* group_sum, int32_t table_chunks,

@@ -137,12 +137,13 @@ class PrefillPipeline:
 class BlockPrefillPipeline:
     """The prompt processed as a sequence of 64-token blocks, each routed
     against the summaries of the chunks closed before it, attended, and then
-    appended to the tables (``hga_prefill_blocks``: one native loop of
-    ``hga_block_step``).  Queries, outputs and the per-block routing results
+    appended to the tables (``hga_prefill_blocks``: what ``hga_block_step``
+    writes block by block, all blocks of the prompt in one launch per step).
+    Queries, outputs and the per-block routing results
     are block-major ([n_blocks, ...]); K/V are the whole prompt's,
     token-indexed, as in the bulk prefill.  ``split_attend``: the blocks'
-    attention in its split form (a workspace spreads each block's few units
-    over more workgroups); without it every output is bit-identical to the
+    attention in its split form, ``hga_block_step``'s with a workspace;
+    without it every output is bit-identical to the
     bulk prefill's."""
 
     def __init__(self, w, inputs: dict, device="cuda", plan: hga.Plan | None = None,
@@ -286,8 +287,7 @@ class DecodePipeline:
                                 self.group_sum, k_chunk0=self.c - self.cur_slot, stream=stream)
 
     def gather_attend(self, stream=None):
-        """The routed groups copied from pinned host memory by the split
-        attention's own workgroups while the others attend the resident chunks."""
+        """The gather from pinned host memory and the attention in one call."""
         hga.hga_gather_attend_split(self.plan, self.q, self.c, self.k_res, self.v_res,
                                     self.k_hist, self.v_hist, self.group_idx, self.k_routed,
                                     self.v_routed, self.out, self.attend_ws, self.lse,
