@@ -464,8 +464,8 @@ def decode_sequence_bench(w, inp, args):
 
 
 def backward_bench(w, inp, args):
-    """The attention backward (hga_attend_backward) of a prefill preset: after
-    one forward step, each timed step zeroes dk, dv and computes dq, dk, dv
+    """The attention backward (hga_attend_backward_write) of a prefill preset:
+    after one forward step, each timed step allocates and writes dq, dk, dv
     for a fixed output gradient.  Roofline: 10*d FLOP per (query, key) pair
     (S recomputed, dP, dQ, dK, dV) against the bf16 matrix-core peak."""
     import torch
@@ -486,17 +486,17 @@ def backward_bench(w, inp, args):
         pipe.backward(dout)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / K
-    # the kernel alone, between events (allocation and zeroing outside)
+    # the call alone, between events (allocation outside)
     from paper_2606_30709_amd import hga
     dq = torch.empty(pipe.q.shape, dtype=torch.float32, device="cuda")
-    dk = torch.zeros(pipe.k.shape, dtype=torch.float32, device="cuda")
-    dv = torch.zeros_like(dk)
+    dk = torch.empty(pipe.k.shape, dtype=torch.float32, device="cuda")
+    dv = torch.empty_like(dk)
     times = []
     for _ in range(max(5, K // 4)):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
-        hga.hga_attend_backward(pipe.plan, pipe.q, 0, pipe.k, pipe.v, pipe.group_idx, pipe.out,
-                                pipe.lse, dout, dq, dk, dv)
+        hga.hga_attend_backward_write(pipe.plan, pipe.q, 0, pipe.k, pipe.v, pipe.group_idx,
+                                      pipe.out, pipe.lse, dout, dq, dk, dv)
         e1.record()
         torch.cuda.synchronize()
         times.append(e0.elapsed_time(e1) * 1e-3)
@@ -520,9 +520,9 @@ def backward_bench(w, inp, args):
 
 
 def blockwise_bench(w, inp, args):
-    """The prompt as a sequence of 64-token blocks (hga_prefill_blocks: per
-    block, routing against the chunks closed so far, gather + attention,
-    then the append of the block's summaries); one step = the whole prompt."""
+    """The prompt as 64-token blocks (hga_prefill_blocks: each routed against
+    the chunks closed before it, all blocks of the prompt together); one step =
+    the whole prompt."""
     import torch
 
     from paper_2606_30709_amd.pipeline import BlockPrefillPipeline
@@ -548,8 +548,8 @@ def blockwise_bench(w, inp, args):
                                 f"{w.dtype}, {w.n_chunks} blocks of {w.chunk} tokens"),
                    "seed": inp["seed"]},
         "us_per_block": round(dt * 1e6 / w.n_chunks, 2),
-        "attention": "split (hga_gather_attend_split)" if split else "hga_gather_attend",
-        "launches_per_block": 4 if split else 3,
+        "attention": "split (hga_block_step's)" if split else "hga_gather_attend",
+        "launches_per_step": 3,
     }
     print(json.dumps(res), flush=True)
 
@@ -599,9 +599,9 @@ def main():
                     help="decode sequence: warm-cache slots per (batch, KV head) "
                          "(default 8 x topk_groups)")
     ap.add_argument("--backward", action="store_true",
-                    help="time the attention backward (hga_attend_backward) of the workload")
+                    help="time the attention backward (hga_attend_backward_write) of the workload")
     ap.add_argument("--block-exact", action="store_true",
-                    help="with --blockwise: the single-workgroup attention whose outputs are "
+                    help="with --blockwise: the unsplit attention, whose outputs are "
                          "bit-identical to the bulk prefill's (default: the split attention)")
     ap.add_argument("--blockwise", action="store_true",
                     help="time the block-sequential prefill (hga_prefill_blocks) instead")
