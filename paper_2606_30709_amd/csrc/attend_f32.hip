@@ -96,10 +96,10 @@ void attend_f32_kernel(
     // consecutive items (the query tiles of one unit, then the next unit) on
     // one XCD, whose L2 then holds the unit's keys
     const int per_xcd = (n_items + kXcds - 1) / kXcds;
-    const int64_t block = linear_block();
-    if (block >= static_cast<int64_t>(per_xcd) * kXcds) return;
-    const int item = static_cast<int>(block % kXcds) * per_xcd + static_cast<int>(block / kXcds);
-    if (item >= n_items) return;
+    const uint32_t block = linear_block<NW * 64>();
+    const int row = static_cast<int>(block / kXcds);  // past per_xcd: beyond the last item
+    const int item = static_cast<int>(block % kXcds) * per_xcd + row;
+    if (row >= per_xcd || item >= n_items) return;
     const int unit_id = tile_div.div(item);
     const int qtile = item - unit_id * tile_div.d;
     const int bh = chunk_div.div(unit_id);

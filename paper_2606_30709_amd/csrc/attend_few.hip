@@ -93,10 +93,10 @@ void attend_few_kernel(
     constexpr int NKS = D / 16, NDT = D / 32;
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int64_t block = linear_block();
+    const int block = static_cast<int>(linear_block<NW * 64>());
     if (block >= n_blocks) return;
-    const int item = tile_div.div(static_cast<uint32_t>(block));
-    const int qtile = static_cast<int>(block) - item * tile_div.d;
+    const int item = tile_div.div(block);
+    const int qtile = block - item * tile_div.d;
     const int bh = chunk_div.div(item);
     const int i = item - bh * n_q_chunks;
     const int64_t unit = unit_map.at(bh, i);
@@ -452,7 +452,7 @@ hipError_t launch_few_t(const hga_plan& plan, const void* q_rot, int q_chunk0, i
     const int waves = n_split < NW ? n_split : NW;
     const int64_t blocks = static_cast<int64_t>(p.batch) * p.n_kv_heads * n_q_chunks * 2 * r;
     if (blocks > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((attend_few_kernel<D, NW, NP, kGather>), grid_of(blocks, waves * 64),
+    hipLaunchKernelGGL((attend_few_kernel<D, NW, NP, kGather>), grid_of(blocks, NW * 64),
                        dim3(waves * 64),
                        FewLayout<D>::bytes(waves), stream, static_cast<const bf16_t*>(q_rot),
                        q_chunk0, n_q_chunks, static_cast<const bf16_t*>(k_res),

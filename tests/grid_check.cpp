@@ -14,7 +14,8 @@ int main() {
             const dim3 g = hga::grid_of(n, threads);
             const int64_t x = g.x, y = g.y;
             const bool ok = x * threads < x_threads && y <= 65535 && g.z == 1 && x * y >= n &&
-                            x * (y - 1) < n && (y == 1 ? x == n : x % 8 == 0);
+                            x * y < int64_t(1) << 31 && x * (y - 1) < n &&
+                            (y == 1 ? x == n : x % 8 == 0 && x == hga::grid_row(threads));
             if (ok) continue;
             std::printf("%lld workgroups of %d: %u x %u x %u\n", static_cast<long long>(n), threads, g.x,
                         g.y, g.z);
